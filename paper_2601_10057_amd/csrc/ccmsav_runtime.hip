@@ -186,7 +186,7 @@ Layout layout(const ccmsav_params* p) {
   L.mid = off;   off = align_up(off + M_NFIELD * sf * me);
   L.outc = off;  off = align_up(off + 2 * sf * me);
   L.part1 = off;
-  off = align_up(off + (size_t)stencil_shape(p->nx, p->ny).blocks * P1_NSUM * sizeof(double));
+  off = align_up(off + (size_t)stencil_shape(p->nx, p->ny).units * P1_NSUM * sizeof(double));
   L.part2 = off; off = align_up(off + p2_rows(p) * P2_NSUM * sizeof(double));
   L.parte = off; off = align_up(off + (size_t)p->ny * E_NSUM * sizeof(double));
   L.lamx = off;  off = align_up(off + (size_t)p->nx * sizeof(double));
@@ -487,7 +487,7 @@ struct ccmsav_ctx {
   std::vector<hipEvent_t> bevent;
   hipEvent_t ev_fork = nullptr;
   // resident workgroups of the stencil pass on this device ([0] FP32, [1] FP64 intermediates)
-  int stencil_slots[2] = {0, 0};
+  int stencil_slots[2] = {-1, -1};
 };
 
 namespace {
@@ -508,7 +508,7 @@ MemberArgs member_args(const Member& m, int precision, int table) {
   a.mob_e = to_global(m.mob_e);
   a.mob_n = to_global(m.mob_n);
   a.iters = m.sh.iters;
-  a.p1_blocks = m.sh.blocks;
+  a.p1_blocks = m.sh.units;
   a.p2_rows = (int)p2_rows(&m.p);
   if (table == kPcgTable) {
     // The classical scheme's preconditioner alpha - lambda M_bar Delta_h for
@@ -570,27 +570,33 @@ MemberArgs member_args(const Member& m, int precision, int table) {
   return a;
 }
 
-// Workgroups of a stencil launch over `total` bands: as many as stay resident
-// on the device at once (a multiple of 8, one share per XCD), or `total` if
-// that is smaller. Measured at N = 4096, the resident grid helps the FP32
-// path (313 -> 303 us) and slows the FP64 one (411 -> 422 us), which keeps
-// one workgroup per band.
-int stencil_grid(ccmsav_ctx* c, bool fp64, int total) {
-  if (fp64) return total;
-  int& slots = c->stencil_slots[fp64 ? 1 : 0];
-  if (slots == 0) {
+// Workgroups of the stencil kernel that stay resident on the device at once
+// (a multiple of 8, one share per XCD; 0 if unknown).
+template <typename TM> int stencil_slots(ccmsav_ctx* c) {
+  int& slots = c->stencil_slots[sizeof(TM) == 8 ? 1 : 0];
+  if (slots < 0) {
     int dev = 0, cus = 0, per_cu = 0;
     (void)hipGetDevice(&dev);
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       cus = 0;
-    const hipError_t e =
-        fp64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_stencil<double>,
-                                                             STENCIL_THREADS, 0)
-             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_stencil<float>,
-                                                            STENCIL_THREADS, 0);
-    slots = (e == hipSuccess && cus > 0 && per_cu > 0) ? (cus * per_cu) & ~7 : -1;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per_cu, k_stencil<TM>, STENCIL_THREADS, 0);
+    slots = e == hipSuccess && cus > 0 && per_cu > 0 ? (cus * per_cu) & ~7 : 0;
   }
-  return (slots <= 0 || total <= slots) ? total : slots;
+  return slots;
+}
+
+// The stencil pass of all members of class k (units and their split:
+// stencil_shape, stencil_split).
+template <typename TM>
+void launch_stencil(ccmsav_ctx* c, const SizeClass& k, const MemberArgs* tab, hipStream_t st) {
+  const bool split = stencil_split(k.sh, stencil_grouped(1 << k.lx, 1 << k.ly), k.count);
+  const int per = split ? k.sh.units : (k.sh.units + SW_WAVES - 1) / SW_WAVES;
+  const int total = (k.count * per + 7) & ~7;
+  const int slots = stencil_slots<TM>(c);
+  const int grid = slots > 0 && total > slots ? slots : total;
+  hipLaunchKernelGGL(k_stencil<TM>, dim3(grid), dim3(STENCIL_THREADS), 0, st, tab, k.d_idx, per,
+                     k.count, total, split ? 1 : 0);
 }
 
 // Autotuner: at the first step every variant of each tuned kernel is run
@@ -657,7 +663,7 @@ void enqueue_classical_solves(ccmsav_ctx* c, int table, hipStream_t st) {
     hipLaunchKernelGGL(k_cl_scalars<CL_RZ>, dim3(1), dim3(512), 0, st, m.cl_part, rows, m.cl_sc,
                        m.ds, (double)n, 0);
   };
-  hipLaunchKernelGGL(k_cl_setup, dim3(1), dim3(512), 0, st, m.part1, m.sh.blocks,
+  hipLaunchKernelGGL(k_cl_setup, dim3(1), dim3(512), 0, st, m.part1, m.sh.units,
                      const_cast<MemberArgs*>(pre), m.cl_sc, sc.alpha, m.p.lam, c->pcg_tol,
                      (double)n);
   hipLaunchKernelGGL(k_cl_start, dim3(CL_BLOCKS), dim3(CL_THREADS), 0, st, b, m.cl_x, m.cl_r,
@@ -716,9 +722,7 @@ void enqueue_step_kind(ccmsav_ctx* c, int table, hipStream_t st, PhaseEvents pe,
   for (size_t ki = 0; ki < c->cls.size(); ++ki) {
     if (skip(ki)) continue;
     const SizeClass& k = c->cls[ki];
-    const int total = k.count * k.sh.blocks;
-    hipLaunchKernelGGL(k_stencil<TM>, dim3(stencil_grid(c, sizeof(TM) == 8, total)),
-                       dim3(STENCIL_THREADS), 0, st, tab, k.d_idx, k.sh.blocks, total);
+    launch_stencil<TM>(c, k, tab, st);
   }
   if constexpr (sizeof(TM) == 8) {
     if (c->classical) enqueue_classical_solves(c, table, st);
@@ -887,8 +891,7 @@ int enqueue_step_gemm(ccmsav_ctx* c, int64_t level, hipStream_t st, PhaseEvents 
   float* mid = static_cast<float*>(m.mid);
   float* outc = static_cast<float*>(m.outc);
   pe.mark(0, st);
-  hipLaunchKernelGGL(k_stencil<float>, dim3(stencil_grid(c, false, k.sh.blocks)),
-                     dim3(STENCIL_THREADS), 0, st, tab, k.d_idx, k.sh.blocks, k.sh.blocks);
+  launch_stencil<float>(c, k, tab, st);
   pe.mark(1, st);
   pe.mark(2, st);
   gemm_dct_rows(m, st, rm, mid, M_NFIELD * ny, false);
@@ -938,8 +941,7 @@ int enqueue_step_periodic(ccmsav_ctx* c, int64_t level, hipStream_t st, PhaseEve
   auto field = [&](int f) { return rm + (size_t)f * cells; };
   const PerConst pc{sc.C1, sc.C2, sc.C3, sc.alpha, sc.lam, m.p.h};
   pe.mark(0, st);
-  hipLaunchKernelGGL(k_stencil<double>, dim3(stencil_grid(c, true, k.sh.blocks)),
-                     dim3(STENCIL_THREADS), 0, st, tab, k.d_idx, k.sh.blocks, k.sh.blocks);
+  launch_stencil<double>(c, k, tab, st);
   pe.mark(1, st);
   pe.mark(2, st);
   int r = periodic_solve_pc(m, c->precision, st, field(M_F), field(M_F), nullptr, pc);
@@ -995,14 +997,16 @@ int build_persist_plan(ccmsav_ctx* c) {
     const SizeClass& k = c->cls[ki];
     // every member of the class takes the 256-thread 5x5 kernel in both paths
     if (solve_threads((size_t)1 << (k.lx + k.ly)) != SOLVE_THREADS_SMALL) return CCMSAV_EUNSUPPORTED;
-    pl.cls[ki] = PersistClass{k.lx, k.ly, k.count, k.d_idx, k.sh.blocks};
+    // one wave per unit: the workgroups of the unsplit stencil pass
+    const int sblocks = (k.sh.units + SW_WAVES - 1) / SW_WAVES;
+    pl.cls[ki] = PersistClass{k.lx, k.ly, k.count, k.d_idx, sblocks};
     const int nx = 1 << k.lx, ny = 1 << k.ly;
     for (int ph = 0; ph < PS_PHASES; ++ph) {
       const int n = (ph == 1 || ph == 5) ? nx : ny;
       const int nt = ps_body_threads<float>(ph, n);
       if (nt > PS_THREADS || PS_THREADS % nt != 0) return CCMSAV_EUNSUPPORTED;
       const int g = PS_THREADS / nt;
-      const long total = (long)k.count * ps_blocks_per_member<float>(ph, nx, ny, k.sh.blocks);
+      const long total = (long)k.count * ps_blocks_per_member<float>(ph, nx, ny, sblocks);
       if (total % g != 0) return CCMSAV_EUNSUPPORTED;
       pl.off[ph][ki + 1] = pl.off[ph][ki] + (int)(total / g);
     }

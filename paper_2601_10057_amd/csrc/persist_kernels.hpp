@@ -155,9 +155,9 @@ __device__ __forceinline__ void ps_stencil(const PersistClass& c, int grp,
                                            const MemberArgs* __restrict__ tab, char* smem) {
   const MemberArgs& m = tab[c.idx[grp / c.sblocks]];
   const RowArgs a{m.phn, m.phm, m.phmm, m.psn, m.psm, m.psmm};
-  stencil_body<TM>(a, static_cast<gptr<TM>>(m.rm), m.part1, m.nx, m.ny, m.iters, m.k,
-                   grp % c.sblocks, m.mob_e, m.mob_n, *reinterpret_cast<StencilLds*>(smem),
-                   (int)threadIdx.x);
+  stencil_body<TM>(a, static_cast<gptr<TM>>(m.rm), m.part1, m.nx, m.ny, m.iters,
+                          m.k, grp % c.sblocks, false, m.mob_e, m.mob_n,
+                          *reinterpret_cast<StencilLds*>(smem), (int)threadIdx.x);
 }
 
 template <typename TM, int NX>

@@ -200,7 +200,7 @@ struct MemberArgs {
   gptr<double> mob_n;            //   of each cell (0 on the walls), written by the stencil
   gptr<const int> skip;          // solve kernels return at once while *skip != 0
   int nx, ny;
-  int iters, p1_blocks;          // stencil launch shape
+  int iters, p1_blocks;          // stencil units: rows of each, number (rows of partial sums)
   int p2_rows;                   // rows of column partial sums
   int chi_base, nchi, zeta_base, nzeta;   // field groups combined by the column solve
   StepConst k;

@@ -259,27 +259,27 @@ __device__ __forceinline__ double lane_from_above(double v) {
                           __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xf, 0xf, false));
 }
 
-// P1a: the stencil terms of a band of rows. Each wave owns SW_OUT consecutive
-// output columns plus two halo columns on either side (64 lanes); walking down
-// the band, a lane keeps the rows above and below the current one in
-// registers and takes the values at the left and right neighbours from the
-// adjacent lanes, so every pointwise quantity (phi*, psi*, P~ and its sine) is
-// formed once per cell. Neighbours outside the grid are the ghost copies of
-// App. D (index clamping), or with periodic boundaries the cells on the other
-// side of the grid (index wrapping). The eight fields are the right-hand sides of
-// eqs. (AC_BDF2)-(Z_BDF2) at phi* = x0 phi^n + x1 phi^{n-1} (slot order of Mid)
-// and leave row-major ([field][ny][nx], x fastest).
+// P1a: the stencil terms of a unit: SW_OUT consecutive output columns of a
+// band of rows, walked by one wave (64 lanes: two halo columns on either
+// side). Walking down the band, a lane keeps the rows above and below the
+// current one in registers and takes the values at the left and right
+// neighbours from the adjacent lanes, so every pointwise quantity (phi*,
+// psi*, P~ and its sine) is formed once per cell. Neighbours outside the grid
+// are the ghost copies of App. D (index clamping), or with periodic
+// boundaries the cells on the other side of the grid (index wrapping). The
+// eight fields are the right-hand sides of eqs. (AC_BDF2)-(Z_BDF2) at phi* =
+// x0 phi^n + x1 phi^{n-1} (slot order of Mid) and leave row-major
+// ([field][ny][nx], x fastest). Each unit leaves one row of partial sums.
 constexpr int STENCIL_THREADS = 256;
 constexpr int SW_WAVES = STENCIL_THREADS / 64;
-constexpr int SW_OUT = 60;                    // output columns per wave
-constexpr int SW_COLS = SW_WAVES * SW_OUT;    // output columns per workgroup
-constexpr int SW_BAND = 32;                   // rows per workgroup (ny if smaller)
+constexpr int SW_OUT = 60;                    // output columns per unit
+constexpr int SW_GROUP = 4;                   // rows per trip of the row loop
 
 // LDS of one invocation of a kernel body, its arrays gathered in one struct:
 // the kernels declare one as __shared__, and the persistent step kernel
 // places several side by side and reuses the space from phase to phase.
 struct StencilLds {
-  double red[P1_NSUM * (STENCIL_THREADS / 64 + 1)];
+  double acc[SW_WAVES][P1_NSUM][64];          // per wave, sum and lane
 };
 // A transform line (or band of lines) and the twiddle roots of length N.
 template <typename TM, int LINE, int N> struct LinesLds {
@@ -287,37 +287,95 @@ template <typename TM, int LINE, int N> struct LinesLds {
   cpx<double> rtab[Roots<TM, N>::SIZE];
 };
 
-// Launch shape of P1a for an nx x ny grid: rows per workgroup and the number
-// of workgroups (one row of partial sums each). A grid of 1024 rows or more
-// that would give fewer than 2048 workgroups (eight per CU) takes bands of 16
-// rows instead of 32: at N = 2048 the 576 workgroups of 32-row bands left
-// most CUs with two (stencil 112 us; 16-row bands 98 us, 8-row bands 97 us).
-// Smaller grids keep 32 rows: they share their launches with the other
-// members of an ensemble, which fill the device.
+// Units of P1a for an nx x ny grid: rows per unit and the number of units.
+// The kernel holds two waves per SIMD, 2048 at once, and a unit costs its
+// rows and about four more (halo rows and the first loads' latency).
+//  - Grids of more than SW_SMALL rows x segments: the band height gives a
+//    whole number of rounds of 2048 units at the least rows per wave slot.
+//    Large grids are bound by memory (N = 4096, mixed: 313 us for 80 B/cell,
+//    4.3 TB/s; bands of 32 rows on 240-column workgroups took 315), at
+//    N = 2048 and 1024 the balance tells: 98 -> 85 us and 36 -> 30 us.
+//  - Smaller grids do not fill the device by themselves, and share it with
+//    other members in an ensemble: units of 16 rows, whose sums are formed
+//    group by group (four rows) in a fixed order, so that a launch may give a
+//    unit to one wave, or to the four waves of a workgroup, with the same
+//    bits (stencil_split). A lone small grid is bound by the row loop's
+//    latency, about 1 us a row: 32-row bands took 41 us at N = 128 and 44 us
+//    at N = 512, four rows per wave 12 and 15 us. In an ensemble the one-wave
+//    form costs less halo (48 x 256^2 + 16 x 512^2: 220 -> 178 us, most of it
+//    from units of 60 columns in place of workgroups of 240).
 struct StencilShape {
-  int iters, blocks;
+  int iters, units;
 };
-constexpr int SW_BAND_MIN = 16;
-constexpr int SW_FILL_BLOCKS = 2048;
+constexpr int SW_SLOTS = 2048;
+constexpr int SW_SMALL = SW_SLOTS * SW_GROUP;
+constexpr int SW_UNIT_ROWS = SW_WAVES * SW_GROUP;
+__host__ __device__ inline int stencil_segments(int nx) { return (nx + SW_OUT - 1) / SW_OUT; }
+__host__ __device__ inline bool stencil_grouped(int nx, int ny) {
+  return stencil_segments(nx) * ny <= SW_SMALL;
+}
 inline StencilShape stencil_shape(int nx, int ny) {
-  const int nseg = (nx + SW_COLS - 1) / SW_COLS;
-  int iters = ny < SW_BAND ? ny : SW_BAND;
-  if (ny >= 1024 && nseg * (ny / iters) < SW_FILL_BLOCKS && iters == SW_BAND) iters = SW_BAND_MIN;
-  return {iters, nseg * (ny / iters)};
+  const int nseg = stencil_segments(nx);
+  int iters = SW_UNIT_ROWS;                   // ny is at least 16
+  if (!stencil_grouped(nx, ny)) {
+    int best = 0;
+    for (int rounds = 1; rounds <= 4; ++rounds) {
+      const int bands = rounds * SW_SLOTS / nseg;
+      const int rows = ((ny + bands - 1) / bands + SW_GROUP - 1) / SW_GROUP * SW_GROUP;
+      const int cost = rounds * (rows + 4);
+      if (best == 0 || cost < best) {
+        best = cost;
+        iters = rows;
+      }
+    }
+  }
+  return {iters, nseg * ((ny + iters - 1) / iters)};
+}
+// Whether `count` grids of `units` 16-row units run one unit per workgroup
+// (four rows per wave) instead of one per wave: while the device then still
+// holds all waves at once.
+inline bool stencil_split(const StencilShape& sh, bool grouped, int count) {
+  return grouped && (long)count * sh.units * SW_WAVES <= SW_SLOTS;
 }
 
+// Sums of the 64 lanes of acc (one unit), by 64 or 256 threads: thread t adds
+// four lanes of sum t / 16 (and so on), then 16 threads add their parts
+// pairwise: the same order for any number of threads.
+template <int NTHR>
+__device__ __forceinline__ void stencil_reduce(const double (&acc)[P1_NSUM][64],
+                                               gptr<double> __restrict__ row, int t) {
+  static_assert(P1_NSUM == 16, "16 sums of 16 parts");
+#pragma unroll
+  for (int q0 = 0; q0 < P1_NSUM; q0 += NTHR / 16) {
+    const int q = q0 + t / 16, l = 4 * (t & 15);
+    double v = ((acc[q][l] + acc[q][l + 1]) + acc[q][l + 2]) + acc[q][l + 3];
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
+    if ((t & 15) == 0) row[q] = v;
+  }
+}
+
+// split: the workgroup's four waves share the 16-row unit `blk`, four rows
+// each; otherwise wave w takes unit blk SW_WAVES + w. (A run-time choice, so
+// that both run the same code: instantiated apart, the compiler fuses
+// products and sums differently and the last bits differ.)
 template <typename TM>
 __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restrict__ rm,
                                              gptr<double> __restrict__ part, int nx, int ny,
-                                             int iters, const StepConst& c, int blk,
+                                             int iters, const StepConst& c, int blk, bool split,
                                              gptr<double> mob_e, gptr<double> mob_n,
                                              StencilLds& L, int tid) {
   constexpr bool INC = increment_form<TM>();
-  double* red = L.red;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int nseg = (nx + SW_COLS - 1) / SW_COLS;
-  const int seg = blk % nseg, band = blk / nseg;
-  const int ci = seg * SW_COLS + wave * SW_OUT - 2 + lane;   // this lane's column
+  // the same for all lanes of a wave
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nseg = stencil_segments(nx);
+  const int unit = split ? blk : blk * SW_WAVES + wave;
+  const int seg = unit % nseg, band = unit / nseg;
+  // the last workgroup's spare waves walk no rows (j1 < j0 below), but keep
+  // to the workgroup's barriers
+  const bool spare = !split && band * iters >= ny;
+  const bool grouped = split || stencil_grouped(nx, ny);
+  const int ci = seg * SW_OUT - 2 + lane;     // this lane's column
   const bool per = c.periodic != 0;
   // the column this lane loads: its ghost source (clamped, or wrapped)
   const int cl = per ? ((ci % nx) + nx) % nx : min(max(ci, 0), nx - 1);
@@ -325,7 +383,8 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
   // Neumann ghosts at the west and east walls are the cell itself; periodic
   // neighbours are the adjacent lanes, which hold the wrapped columns
   const bool at_w = !per && ci == 0, at_e = !per && ci == nx - 1;
-  const int j0 = band * iters;
+  const int j0 = band * iters + (split ? wave * SW_GROUP : 0);
+  const int j1 = split ? j0 + SW_GROUP : min(j0 + iters, ny);
   const size_t FS = (size_t)nx * ny;
   const double k32 = 0.75 * 1.4142135623730950488;   // 3 sqrt(2) / 4
   const double half_pi = 1.5707963267948966192;
@@ -534,24 +593,60 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
     m_south = Mn;
     rs = rc;
     rc = rn;
-    if (j + 1 < j0 + iters) rn = make_row(r2);
+    if (j + 1 < j1) rn = make_row(r2);
     Ls = Lc;
     Lc = Ln;
   };
+  // acc[q][lane] += the lane's sums, which start again at zero
+  auto& acc = L.acc[wave];
+  auto flush = [&](bool first) {
+#pragma unroll
+    for (int q = 0; q < P1_NSUM; ++q) {
+      acc[q][lane] = first ? sums[q] : acc[q][lane] + sums[q];
+      sums[q] = 0.0;
+    }
+  };
   Raw r0 = load_raw(j0 + 2), r1 = load_raw(j0 + 3);
+  // On large grids the workgroup's waves keep in step: neighbouring units
+  // share the cache lines at their seams, and written at different times
+  // these leave as partial sectors (N = 8192: 1396 us without the barrier,
+  // 1284 us with it; N = 4096 FP64 427 and 400 us).
+  const int j2 = split ? j1 : j0 + iters;
 #pragma unroll 1
-  for (int j = j0; j < j0 + iters; j += 4) {
+  for (int j = j0; j < j2; j += SW_GROUP) {
+    if (!grouped) __builtin_amdgcn_s_barrier();
+    if (j >= j1) continue;
     const Raw r2 = load_raw(j + 4);
     row_step(j, r0);
     const Raw r3 = load_raw(j + 5);
     row_step(j + 1, r1);
-    if (j + 4 < j0 + iters) r0 = load_raw(j + 6);
+    if (j + 4 < j1) r0 = load_raw(j + 6);
     row_step(j + 2, r2);
-    if (j + 4 < j0 + iters) r1 = load_raw(j + 7);
+    if (j + 4 < j1) r1 = load_raw(j + 7);
     row_step(j + 3, r3);
+    if (grouped && j + 4 < j1) flush(j == j0);
   }
-  block_sum<P1_NSUM, STENCIL_THREADS>(sums, red, tid);
-  if (tid < P1_NSUM) part[(size_t)blk * P1_NSUM + tid] = red[tid];
+  const auto row = part + (size_t)unit * P1_NSUM;
+  if (split) {
+    flush(true);
+    lds_sync();
+    // the four groups, in order, as one wave adds them
+    double* g = &L.acc[0][0][0];
+    constexpr int GS = P1_NSUM * 64;
+    for (int e = tid; e < GS; e += STENCIL_THREADS)
+      g[e] = ((g[e] + g[e + GS]) + g[e + 2 * GS]) + g[e + 3 * GS];
+    lds_sync();
+    stencil_reduce<STENCIL_THREADS>(L.acc[0], row, tid);
+  } else if (!spare) {
+    flush(!grouped || j1 - j0 <= SW_GROUP);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    stencil_reduce<64>(acc, row, lane);
+    // the wave's next unit overwrites acc
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 // Column-pair piece of one field over the rows of a workgroup, stored with one
@@ -1988,23 +2083,23 @@ __device__ __forceinline__ const MemberArgs& batch_member(const MemberArgs* __re
 }
 
 // The stencil pass runs as a resident grid: workgroup b takes virtual blocks
-// (bands) vb until all `total` are done, each XCD working through a
-// contiguous range of them, so that no half-empty last wave of workgroups is
-// left on the chip.
+// vb until all `total` (a multiple of 8 with at most 7 past the last member's)
+// are done, each XCD working through a contiguous range of them, so that
+// neighbouring units share an L2.
 template <typename TM>
-__global__ void __launch_bounds__(STENCIL_THREADS) k_stencil(BATCH_PARAMS, int total) {
+__global__ void __launch_bounds__(STENCIL_THREADS)
+k_stencil(BATCH_PARAMS, int count, int total, int split) {
   __shared__ StencilLds L;
   const int g = gridDim.x, b = blockIdx.x;
-  const bool xcd = (g & 7) == 0 && (total & 7) == 0;
-  const int first = xcd ? (b & 7) * (total >> 3) + (b >> 3) : b;
-  const int last = xcd ? (b & 7) * (total >> 3) + (total >> 3) : total;
-  const int step = xcd ? g >> 3 : g;
-  for (int vb = first; vb < last; vb += step) {
+  const int share = total >> 3, last = (b & 7) * share + share;
+  for (int vb = (b & 7) * share + (b >> 3); vb < last; vb += g >> 3) {
+    if (vb >= count * per) return;            // whole workgroup
     const int blk = vb % per;
     const MemberArgs& m = tab[idx[vb / per]];
     const RowArgs a{m.phn, m.phm, m.phmm, m.psn, m.psm, m.psmm};
     stencil_body<TM>(a, static_cast<gptr<TM>>(m.rm), m.part1, m.nx, m.ny, m.iters, m.k, blk,
-                     m.mob_e, m.mob_n, L, threadIdx.x);
+                     split != 0, m.mob_e, m.mob_n, L, threadIdx.x);
+    if (split) lds_sync();                    // the next unit overwrites the sums
   }
 }
 
