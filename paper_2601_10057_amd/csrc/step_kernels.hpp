@@ -1029,6 +1029,8 @@ __device__ __forceinline__ void col_gram_body(gptr<const TM> __restrict__ mid,
   const size_t FSM = strip_field(nx, NY, sizeof(TM));
   Roots<TM, NY> rt;
   rt.init(rtab, tid, NTHR);
+  // a first stage from registers looks the roots up before any other barrier
+  lds_sync();
   const LS sl(tid);
   if constexpr (ACC_LDS) {
 #pragma unroll
