@@ -137,11 +137,11 @@ size_t gemm_gram_blocks(const ccmsav_params* p) {
 bool is_periodic(const ccmsav_params* p) { return (p->flags & CCMSAV_FLAG_PERIODIC) != 0; }
 bool is_classical(const ccmsav_params* p) { return (p->flags & CCMSAV_FLAG_CLASSICAL) != 0; }
 bool is_persistent(const ccmsav_params* p) { return (p->flags & CCMSAV_FLAG_PERSISTENT) != 0; }
-// Rows of inner-product partials: one per strip (spectral path), per block of
+// Rows of inner-product partials: one per column (spectral path), per block of
 // cells (DCT-as-GEMM) or per grid row (periodic step, physical space).
 size_t p2_rows(const ccmsav_params* p) {
   if (is_periodic(p)) return (size_t)p->ny;
-  return is_gemm(p->precision) ? gemm_gram_blocks(p) : (size_t)(p->nx / 2);
+  return is_gemm(p->precision) ? gemm_gram_blocks(p) : (size_t)p->nx;
 }
 
 // DCT-as-GEMM variant: a direction of n points takes the factored transform
@@ -742,7 +742,7 @@ void enqueue_step_kind(ccmsav_ctx* c, int table, hipStream_t st, PhaseEvents pe,
   for (size_t ki = 0; ki < c->cls.size(); ++ki) {
     if (skip(ki)) continue;
     const SizeClass& k = c->cls[ki];
-    const int per = (1 << k.lx) / 2;
+    const int per = 1 << k.lx;     // one workgroup per column
     LT::t_gram[k.ly - kMinLog](st, k.count * per, Batch{tab, k.d_idx, per});
   }
   pe.mark(5, st);

@@ -55,7 +55,7 @@ def fft_radix(esz):
 
 def gram_radix(esz, n):
     q = n // gram_threads(esz, n)
-    return 8 if q >= 8 else (4 if q >= 4 else 2)
+    return 16 if q >= 16 else (8 if q >= 8 else (4 if q >= 4 else 2))
 
 
 def lds_line_budget(esz, n):

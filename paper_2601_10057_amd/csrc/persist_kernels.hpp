@@ -64,7 +64,7 @@ inline int ps_blocks_per_member(int pass, int nx, int ny, int sblocks) {
   switch (pass) {
     case 0: return sblocks;
     case 1: return ny / p1_rows_v<TM>(nx, PS_ROW_DCT_V);
-    case 2: return nx / 2;
+    case 2: return nx;
     case 3: return 1;
     case 4: return nx;                      // two groups (chi, zeta) per strip
     default: return ny / row_idct_rows<TM>(nx, 0);
@@ -181,7 +181,7 @@ __device__ __attribute__((noinline)) void ps_gram(const PersistClass& c, int grp
   constexpr int NT = gram_threads<TM>(NY), G = PS_THREADS / NT;
   using L = GramLds<TM, NY>;
   const int sg = (int)threadIdx.x / NT;
-  const int per = (1 << c.lx) / 2;
+  const int per = 1 << c.lx;
   const int vb = grp * G + sg;
   const MemberArgs& m = tab[c.idx[vb / per]];
   const OpConst o{m.k.C1, m.k.C2, m.k.C3, m.k.alpha, m.k.lam};

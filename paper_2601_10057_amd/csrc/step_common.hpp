@@ -151,8 +151,8 @@ __host__ __device__ constexpr size_t strip_field(int nx, int ny, int esize) {
 }
 
 // FP32 intermediates store the fields in pairs: the two fields of a pair share
-// one region, interleaved per row (row j of strip s holds f(2s, j), f(2s+1, j),
-// f'(2s, j), f'(2s+1, j): 16 bytes). The row pass then writes a band of rows of
+// one region, interleaved per row (row j of strip s holds f(2s, j), f'(2s, j),
+// f(2s+1, j), f'(2s+1, j): 16 bytes). The row pass then writes a band of rows of
 // both fields as one piece (64 bytes for four rows), and the column passes
 // load a row of both fields with one 16-byte load. The pairs follow the order
 // in which the Gram pass transforms the fields: (S~, H), (Q~, K~), (f_lin, P~),
@@ -190,7 +190,7 @@ struct MemberArgs {
   gptr<void> mid;                // 8 x-transformed fields, strip-major
   gptr<void> outc;               // 2 y-solved fields, strip-major
   gptr<double> part1;            // stencil partial sums, one row per workgroup
-  gptr<double> part2;            // column partial sums, one row per strip
+  gptr<double> part2;            // column partial sums, one row per column
   gptr<const double> lamx;       // (4/h^2) sin^2(pi k / (2 n)) per direction
   gptr<const double> lamy;
   gptr<double> colsum;           // increment form: row-sum targets of the psi increment

@@ -51,6 +51,9 @@ __device__ __forceinline__ int opaque_vgpr(int x) {
   return x;
 }
 
+// Computes x here: what it is formed from need not be held any longer.
+__device__ __forceinline__ void pin_vgpr(double& x) { __asm__ volatile("" : "+v"(x)); }
+
 constexpr int clamp_threads(int t) { return t < 64 ? 64 : (t > 1024 ? 1024 : t); }
 // Threads of a line kernel: four elements per thread.
 constexpr int line_threads(int n) { return clamp_threads(n / 4); }
@@ -63,13 +66,18 @@ template <typename TM> constexpr int one_line_threads(int n) {
 template <typename TM> constexpr int line_threads_v(int n, int v) {
   return v == 0 ? line_threads(n) : one_line_threads<TM>(n);
 }
-// The Gram kernel keeps four spectra per thread: eight bins per thread give
-// each wave up to 256 registers at one workgroup per CU. FP32 lines of 8192
-// points and more take sixteen bins per thread (workgroups of 8 waves, up to
-// 256 registers each) and keep their spectra in global memory.
+// Threads of the Gram kernel, one workgroup per column: eight bins per
+// thread, so that four kept FP32 spectra take 32 registers and two workgroups
+// of 512 threads fit a CU at N = 4096. FP32 lines of 8192 points take sixteen
+// bins and radix-16 butterflies: one workgroup per CU either way (1024
+// threads: 1594 us, 512: 1499).
 template <typename TM> constexpr int gram_threads(int n) {
   return clamp_threads(n / (sizeof(TM) == 4 && n >= 8192 ? 16 : 8));
 }
+// Waves per SIMD the Gram kernel's registers are held to: it is bound by issue
+// and by barriers, so lines of 2048 and 4096 points take four at 128 registers
+// (N = 4096 FP64: 475 us against 590 at two; N = 2048 FP32 66 against 78).
+constexpr int gram_waves(int n) { return n == 2048 || n == 4096 ? 4 : 1; }
 // Complex lines of length n that fit in LDS next to the twiddle tables.
 template <typename TM> constexpr int lds_line_budget(int n) {
   return (136 * 1024) / (n * (int)sizeof(cpx<TM>));
@@ -134,9 +142,17 @@ template <typename TM>
 __device__ __forceinline__ size_t mid_offset(int f, int k, int j, int nx, int ny) {
   if constexpr (sizeof(TM) == 4)
     return mid_pair(f) * pair_field(nx, ny) + (size_t)(k >> 1) * pair_strip_stride(ny) +
-           4 * (size_t)j + 2 * mid_half(f) + (k & 1);
+           4 * (size_t)j + 2 * (k & 1) + mid_half(f);
   else
     return f * strip_field(nx, ny, sizeof(TM)) + mid_index(k, j, strip_stride(ny, sizeof(TM)));
+}
+
+// Orders a wave's LDS writes before its own later reads and writes (the
+// lanes of a wave run together; this only keeps the compiler to the order).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Sum NV doubles over the block in a fixed order; the totals land in red[0..NV).
@@ -639,13 +655,9 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
     stencil_reduce<STENCIL_THREADS>(L.acc[0], row, tid);
   } else if (!spare) {
     flush(!grouped || j1 - j0 <= SW_GROUP);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_sync();
     stencil_reduce<64>(acc, row, lane);
-    // the wave's next unit overwrites acc
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();                // the wave's next unit overwrites acc
   }
 }
 
@@ -804,8 +816,8 @@ __device__ __forceinline__ void row_dct8_body(gptr<const TM> __restrict__ rm,
 #pragma unroll
             for (int q = 0; q < RH; ++q) {
               pc.v[4 * q] = pa.v[2 * q];
-              pc.v[4 * q + 1] = pa.v[2 * q + 1];
-              pc.v[4 * q + 2] = pb.v[2 * q];
+              pc.v[4 * q + 1] = pb.v[2 * q];
+              pc.v[4 * q + 2] = pa.v[2 * q + 1];
               pc.v[4 * q + 3] = pb.v[2 * q + 1];
             }
             const size_t o = (size_t)sp * SSP + 4 * (size_t)(j0 + half * RH);
@@ -849,23 +861,6 @@ __device__ __forceinline__ void fetch_strip(gptr<const cpx<TM>> __restrict__ src
   }
 }
 
-// Both fields of a strip of an FP32 pair region (mid_pair), the thread's
-// rows q = Q0 .. Q1 - 1: row jj is one 16-byte load; a takes the first field,
-// b the second.
-template <typename TM, int NY, int LPT, int NTHR, int Q0, int Q1>
-__device__ __forceinline__ void fetch_pair_strip(gptr<const TM> __restrict__ src, int tid,
-                                                 StripRegs<TM, LPT>& a, StripRegs<TM, LPT>& b) {
-  typedef TM tm4 __attribute__((ext_vector_type(4)));
-  const auto p = reinterpret_cast<gptr<const tm4>>(src);
-#pragma unroll
-  for (int q = Q0; q < Q1; ++q) {
-    const int jj = tid + q * NTHR;
-    const tm4 v = (NY >= NTHR || jj < NY) ? p[jj] : tm4{(TM)0, (TM)0, (TM)0, (TM)0};
-    a.v[q] = {v[0], v[1]};
-    b.v[q] = {v[2], v[3]};
-  }
-}
-
 // Whether the column transform can take its first FFT stage straight from the
 // loaded registers: one radix-R butterfly per thread in every stage, so that
 // thread tid's first butterfly reads Makhoul-ordered elements tid + q (N/R).
@@ -883,22 +878,6 @@ __device__ __forceinline__ void fetch_strip_first(gptr<const cpx<TM>> __restrict
     const int k = tid + q * (NY / R);
     const int row = k < NY / 2 ? 2 * k : 2 * (NY - 1 - k) + 1;
     r.v[q] = gload<TM>(src + row * STRIDE);
-  }
-}
-
-// fetch_strip_first for both fields of an FP32 pair strip, rows q = Q0 .. Q1 - 1.
-template <typename TM, int NY, int R, int NTHR, int Q0, int Q1>
-__device__ __forceinline__ void fetch_pair_strip_first(gptr<const TM> __restrict__ src, int tid,
-                                                       StripRegs<TM, R>& a, StripRegs<TM, R>& b) {
-  typedef TM tm4 __attribute__((ext_vector_type(4)));
-  const auto p = reinterpret_cast<gptr<const tm4>>(src);
-#pragma unroll
-  for (int q = Q0; q < Q1; ++q) {
-    const int k = tid + q * (NY / R);
-    const int row = k < NY / 2 ? 2 * k : 2 * (NY - 1 - k) + 1;
-    const tm4 v = p[row];
-    a.v[q] = {v[0], v[1]};
-    b.v[q] = {v[2], v[3]};
   }
 }
 
@@ -951,54 +930,51 @@ __device__ __forceinline__ void column_dct2(const StripRegs<TM, LPT>& in, cpx<TM
   if constexpr (TRAIL_SYNC) lds_sync();
 }
 
-// Sum NV per-thread values over the block and add them to acc[IDX[q]].
-template <int NV, int NTHR>
-__device__ __forceinline__ void stage_accumulate(double (&v)[NV], const int (&idx)[NV],
-                                                 double* red, double* acc, int tid) {
-  block_sum<NV, NTHR>(v, red, tid);
-  if (tid < NV) acc[idx[tid]] += red[tid];
-}
-
-// LDS plan of the Gram kernel: the line, the S~ spectrum (waiting for its
-// products with the later fields) and, where they fit, per-thread partial
-// sums that are reduced over the block once per strip instead of once per
-// field.
+// Plan of the Gram kernel: its threads and how it uses registers and LDS (a
+// column's line, in two buffers that alternate from pair to pair where that
+// fits, so that a transform needs no barrier after its last reads, and the
+// twiddle roots; the line is at least 2 KB per wave, as the final sums pass
+// through it).
 template <typename TM, int NY> struct GramPlan {
+  static constexpr bool F32 = sizeof(TM) == 4;
   static constexpr int NTHR = gram_threads<TM>(NY);
-  static constexpr int LINE_B = NY * (int)sizeof(cpx<TM>);
-  static constexpr int ROOT_B = Roots<TM, NY>::SIZE * (int)sizeof(cpx<double>);
-  // The partial sums only go to LDS while the CU still holds 8 waves of
-  // workgroups.
-  static constexpr int BUDGET = 150 * 1024;
   static constexpr int WAVES = NTHR / 64;
-  static constexpr int ACC_BUDGET = WAVES >= 8 ? BUDGET : (160 * 1024) / (8 / WAVES);
-  static constexpr int ACC_B = P2_NSUM * NTHR * (int)sizeof(double);
-  // FP32 workgroups of 8 waves (one per CU): two line buffers, alternating
-  // from field to field, where they fit beside the partial sums (the S~
-  // spectrum then stays in registers), so that a transform needs no barrier
-  // after its last reads of its line. (With 4 waves the extra registers would
-  // halve the waves per SIMD.)
-  static constexpr bool DBL = sizeof(TM) == 4 && NTHR == 512 &&
-                              2 * LINE_B + ROOT_B + ACC_B <= ACC_BUDGET;
-  static constexpr bool S_LDS = !DBL && 2 * LINE_B + ROOT_B <= BUDGET;
-  static constexpr bool ACC_LDS =
-      (S_LDS || DBL ? 2 : 1) * LINE_B + ROOT_B + ACC_B <= ACC_BUDGET && NTHR % 16 == 0;
-  // FP32 lines of 8192 points and more: sixteen bins per thread leave no
-  // registers for the kept spectra beside a transform, so they go to
-  // per-thread slots in global memory (the stencil output region, unused
-  // while this pass runs), written once and read once by the same thread,
-  // coalesced across the wave.
-  static constexpr bool KEEP_GLOBAL = NY >= 8192;
+  static constexpr int ELEM = (int)sizeof(cpx<TM>);
+  static constexpr bool DBL = F32 && NTHR == 512;
+  static constexpr int LINE = (DBL ? 2 : 1) * NY;
+  static constexpr int SUMS = WAVES * 4 * 64 * (int)sizeof(double) / ELEM;
+  // The LDS slots formed anew per transform where held ones would spill at
+  // four waves per SIMD (gram_waves). Shorter FP32 lines keep their slots (N
+  // = 1024: 22.6 against 24.6 us).
+  static constexpr bool FRESH = !F32 || NY >= 2048;
+  // The next pair's rows loaded while the current pair is transformed. The
+  // shortest lines are left to the other workgroups of their CU (ensemble of
+  // 48 x 256^2 + 16 x 512^2: 101 us, with loads ahead 113).
+  static constexpr bool AHEAD = F32 && NY >= 1024;
+  // FP64 lines of 8192 points: the kept spectra of eight bins do not fit the
+  // 128 registers of a 1024-thread workgroup, so they go to per-thread slots
+  // in global memory (the stencil output region, unused while this pass
+  // runs), written once and read once by the same thread, coalesced across
+  // the wave.
+  static constexpr bool KEEP_GLOBAL = !F32 && NY >= 8192;
 };
 template <typename TM, int NY> struct GramLds {
   using GP = GramPlan<TM, NY>;
-  cpx<TM> line[(GP::DBL ? 2 : 1) * NY];
-  cpx<TM> keep[GP::S_LDS ? NY : 1];
+  cpx<TM> line[GP::LINE > GP::SUMS ? GP::LINE : GP::SUMS];
   cpx<double> rtab[Roots<TM, NY>::SIZE];
-  double red[GP::ACC_LDS ? 1 : P2_NSUM * (GP::NTHR / 64 + 1)];   // per-field block sums
-  double acc[GP::ACC_LDS ? P2_NSUM * GP::NTHR : P2_NSUM];
+  double wsum[GP::WAVES][P2_NSUM];
 };
 
+// The Gram pass of column k. The eight fields go through the transform in
+// four pairs, two fields of the column as one complex line. A column at a
+// time keeps half of what a strip of two columns would (four spectra of NY
+// values), so that two workgroups of eight waves fit a CU at N = 4096 and
+// fill each other's barriers, and at N = 8192 nothing spills to memory. Both
+// columns of a strip read its rows; the second read is served by the L2 (the
+// counted HBM traffic is that of one). At N = 4096 (FP32, 248 us; two columns
+// per workgroup 253 us) the VALU issues 73% of the time. Two columns side by
+// side in one workgroup of 1024 threads: 290 us; radix 16 with 256 threads:
+// 272 us.
 // FRESH_SLOTS: every transform forms its LDS slots anew (the persistent
 // launch, where the kernel's register budget is shared by all passes).
 template <typename TM, int NY, bool FRESH_SLOTS = false>
@@ -1006,325 +982,172 @@ __device__ __forceinline__ void col_gram_body(gptr<const TM> __restrict__ mid,
                                               gptr<const double> __restrict__ lamx,
                                               gptr<const double> __restrict__ lamy,
                                               gptr<double> __restrict__ part, int nx,
-                                              const OpConst c, int s, GramLds<TM, NY>& L,
+                                              const OpConst c, int k, GramLds<TM, NY>& L,
                                               int tid, gptr<TM> __restrict__ kg) {
   using GP = GramPlan<TM, NY>;
   constexpr int NTHR = GP::NTHR;
-  constexpr int LPT = NY >= NTHR ? NY / NTHR : 1;            // strip loads per thread
+  constexpr int LPT = NY >= NTHR ? NY / NTHR : 1;            // loads per thread
   constexpr int UPT = NY / 2 >= NTHR ? NY / 2 / NTHR : 1;    // pair units per thread
   constexpr int KPT = 2 * UPT;                               // bins per thread
-  constexpr int KS = NY / 2 >= NTHR ? NTHR : NY / 2;         // stride of a thread's bins in keep
   // Radix with one butterfly per thread in each FFT stage.
-  constexpr int GR = NY / NTHR >= 8 ? 8 : (NY / NTHR >= 4 ? 4 : 2);
+  constexpr int GR = NY / NTHR >= 16 ? 16 : NY / NTHR >= 8 ? 8 : NY / NTHR >= 4 ? 4 : 2;
   using MAP = LdsMap<TM, NY, SWZ_GRAM>;
   using LS = LineSlots<NY, NTHR, GR, MAP>;
-  constexpr bool S_LDS = GP::S_LDS;
-  constexpr bool ACC_LDS = GP::ACC_LDS;
-  cpx<TM>* line = L.line;
-  cpx<TM>* keep = L.keep;
-  cpx<double>* rtab = L.rtab;
-  double* red = L.red;
-  double* acc = L.acc;
-  const size_t SS = strip_stride(NY, sizeof(TM));
-  const size_t FSM = strip_field(nx, NY, sizeof(TM));
   Roots<TM, NY> rt;
-  rt.init(rtab, tid, NTHR);
+  rt.init(L.rtab, tid, NTHR);
   // a first stage from registers looks the roots up before any other barrier
   lds_sync();
   const LS sl(tid);
-  if constexpr (ACC_LDS) {
-#pragma unroll
-    for (int q = 0; q < P2_NSUM; ++q) acc[q * NTHR + tid] = 0.0;
-  } else {
-    if (tid < P2_NSUM) acc[tid] = 0.0;
-  }
-  // Adds the thread's stage sums v[b] to sum idx[b].
-  auto accumulate = [&](auto& v, const auto& idx) {
-    constexpr int NV = sizeof(v) / sizeof(double);
-    if constexpr (ACC_LDS) {
-#pragma unroll
-      for (int b = 0; b < NV; ++b) acc[idx[b] * NTHR + tid] += v[b];
-    } else {
-      stage_accumulate<NV, NTHR>(v, idx, red, acc, tid);
-    }
-  };
-  const double lx0 = lamx[2 * s], lx1 = lamx[2 * s + 1];
-  auto strip = [&](int f) {
-    return reinterpret_cast<gptr<const cpx<TM>>>(mid + (size_t)f * FSM + (size_t)s * SS);
-  };
+  const double lx = lamx[k];
+  const bool valid = NY / 2 >= NTHR || tid < NY / 2;
   // bin held at index j (unit tid + (j / 2) NTHR; even j: the unit's own bin)
   auto bin_of = [&](int j) {
     const int u = tid + (j >> 1) * NTHR;
     return (j & 1) ? pair_mirror<NY>(u) : u;
   };
-  const bool valid = NY / 2 >= NTHR || tid < NY / 2;
-  // 1/sigma (chi) or 1/tau (zeta) at (2s, k) and (2s+1, k)
-  auto inv_op = [&](int k, bool chi, double& i0, double& i1) {
-    const double ly = lamy[k];
-    const double L0 = lx0 + ly, L1 = lx1 + ly;
-    if (chi) {
-      i0 = rcp64(c.C1 + L0 * (c.C2 + c.C3 * L0));
-      i1 = rcp64(c.C1 + L1 * (c.C2 + c.C3 * L1));
-    } else {
-      i0 = rcp64(c.alpha + c.lam * L0);
-      i1 = rcp64(c.alpha + c.lam * L1);
-    }
-  };
-  // Spectra kept for the pairwise products: index 0 = S~ (unless in LDS),
-  // 1 = H, 2 = Q~, 3 = K~; later 1 = P~ and 2 = g_lin. With GP::KEEP_GLOBAL
-  // slot f of bin index j is element (f KPT + j) NTHR + tid of this strip's
-  // block of 4 NY complex values in kg.
-  constexpr bool KG = GP::KEEP_GLOBAL;
-  constexpr int KR = KG ? 1 : KPT;
-  TM ka[4][KR], kb[4][KR];
-  typedef TM tm2 __attribute__((ext_vector_type(2)));
-  const auto kgs = reinterpret_cast<gptr<tm2>>(kg) + (size_t)s * 4 * NY + tid;
-  auto kept = [&](int f, int j, TM& a, TM& b) {
-    if (S_LDS && f == 0) {
-      const cpx<TM> v = keep[tid + j * KS];
-      a = v.re;
-      b = v.im;
-    } else if constexpr (KG) {
-      const tm2 v = kgs[(f * KPT + j) * NTHR];
-      a = v[0];
-      b = v[1];
-    } else {
-      a = ka[f][j];
-      b = kb[f][j];
-    }
-  };
-  auto put = [&](int f, int j, TM a, TM b) {
-    if constexpr (KG) {
-      kgs[(f * KPT + j) * NTHR] = tm2{a, b};
-    } else {
-      ka[f][j] = a;
-      kb[f][j] = b;
-    }
-  };
-  // Fields in the order they are transformed. With FP32 lines the fields
-  // come in the pairs of their layout (mid_pair), consecutive in this order:
-  // one 16-byte load per row brings a field and the next. The next pair is
-  // loaded while the current one is transformed, half of its rows during
-  // each of the two transforms. FP64 lines (one field per region) and
-  // workgroups of more than 8 waves (at most 128 registers per thread) have
-  // no registers to spare for loads ahead: they load each field when it is
-  // transformed (FP32: its half of the pair region, the other half read
-  // from L2 one transform later).
-  constexpr int ORDER[8] = {M_S, M_H, M_Q, M_K, M_F, M_P, M_G, M_L};
-  static_assert(mid_pair(ORDER[0]) == mid_pair(ORDER[1]) && mid_half(ORDER[0]) == 0 &&
-                    mid_pair(ORDER[2]) == mid_pair(ORDER[3]) && mid_half(ORDER[2]) == 0 &&
-                    mid_pair(ORDER[4]) == mid_pair(ORDER[5]) && mid_half(ORDER[4]) == 0 &&
-                    mid_pair(ORDER[6]) == mid_pair(ORDER[7]) && mid_half(ORDER[6]) == 0,
-                "the transform order takes the pairs' fields one after the other");
-  constexpr bool PAIRS = sizeof(TM) == 4 && NTHR <= 512 && !GP::KEEP_GLOBAL;
-  // The first FFT stage runs on the loaded registers where every stage has
-  // one butterfly per thread.
+  // The pairs in the order they are transformed, with the fields' slots.
+  // FP32 pairs are those of the layout (mid_pair): a row of the column holds
+  // both fields side by side. FP64 fields lie in a region each.
+  constexpr int FA[4] = {M_S, M_Q, M_F, sizeof(TM) == 4 ? M_G : M_L};
+  constexpr int FB[4] = {M_H, M_K, sizeof(TM) == 4 ? M_P : M_G, sizeof(TM) == 4 ? M_L : M_P};
   constexpr bool FIRST_IN_REGS = first_stage_in_registers<NY, NTHR, GR>() && LPT == GR;
-  auto fetch = [&](int f, StripRegs<TM, LPT>& r) {
-    if constexpr (FIRST_IN_REGS) {
-      fetch_strip_first<TM, NY, GR, NTHR>(strip(f), tid, r);
-    } else {
-      fetch_strip<TM, NY, LPT, NTHR>(strip(f), tid, r);
-    }
-  };
-  // FP32: the fields of pair k in set k % 2
-  StripRegs<TM, LPT> pa[2], pb[2];
-  constexpr int QH = LPT >= 2 ? LPT / 2 : LPT;
-  auto fetch_pair = [&](int f, auto iset, auto iq0, auto iq1) {
-    constexpr int st = decltype(iset)::value, q0 = decltype(iq0)::value,
-                  q1 = decltype(iq1)::value;
-    const auto src = mid + mid_pair(f) * pair_field(nx, NY) + (size_t)s * pair_strip_stride(NY);
-    if constexpr (FIRST_IN_REGS) {
-      fetch_pair_strip_first<TM, NY, GR, NTHR, q0, q1>(src, tid, pa[st], pb[st]);
-    } else {
-      fetch_pair_strip<TM, NY, LPT, NTHR, q0, q1>(src, tid, pa[st], pb[st]);
-    }
-  };
-  using I0 = std::integral_constant<int, 0>;
-  using IH = std::integral_constant<int, QH>;
-  using IL = std::integral_constant<int, LPT>;
-  if constexpr (PAIRS) fetch_pair(ORDER[0], I0{}, I0{}, IL{});
-  // FP32 lines with the kept spectra in global memory: a pair's strip is
-  // loaded once, with 16-byte loads, when its first field is transformed;
-  // the second field waits in registers (loading each half on its own
-  // fetched the pair's sectors twice).
-  constexpr bool KG_PAIR = GP::KEEP_GLOBAL && sizeof(TM) == 4;
-  StripRegs<TM, KG_PAIR ? LPT : 1> kg_second;
-  auto transform_next = [&](auto ii, TM (&A)[KPT], TM (&B)[KPT]) {
-    constexpr int i = decltype(ii)::value;
-    StripRegs<TM, LPT> cur;
-    if constexpr (PAIRS) {
-      constexpr int cs = (i / 2) % 2, ns = 1 - cs;
-      using INS = std::integral_constant<int, ns>;
-      if constexpr (i % 2 == 0) {
-        cur = pa[cs];
-        if constexpr (i + 2 < 8) fetch_pair(ORDER[i + 2], INS{}, I0{}, IH{});
-      } else {
-        cur = pb[cs];
-        if constexpr (i + 1 < 8 && QH < LPT) fetch_pair(ORDER[i + 1], INS{}, IH{}, IL{});
-      }
-    } else if constexpr (GP::KEEP_GLOBAL) {
-      // The eight transforms form their LDS slots (a per-thread base XOR a
-      // constant) from a thread index of their own, so that the compiler
-      // does not hold each slot across the kernel (it spilled them).
-      static_assert(!GP::DBL && !FIRST_IN_REGS, "one line buffer, loads into LDS");
-      const int tt = opaque_vgpr(tid);
-      const LS slt(tt);
-      if constexpr (KG_PAIR) {
-        if constexpr (i % 2 == 0) {
-          const auto src =
-              mid + mid_pair(ORDER[i]) * pair_field(nx, NY) + (size_t)s * pair_strip_stride(NY);
-          fetch_pair_strip<TM, NY, LPT, NTHR, 0, LPT>(src, tt, cur, kg_second);
-        } else {
-          cur = kg_second;
-        }
-      } else {
-        fetch_strip<TM, NY, LPT, NTHR>(strip(ORDER[i]), tt, cur);
-      }
-      column_dct2<TM, NY, LPT, UPT, NTHR, GR, MAP, false, true>(cur, line, rt, slt, tt, A, B);
-      return;
-    } else if constexpr (sizeof(TM) == 4) {
+  auto fetch = [&](auto ip, int t, StripRegs<TM, LPT>& r) {
+    constexpr int p = decltype(ip)::value;
+    const size_t st = (size_t)(k >> 1);
+    if constexpr (sizeof(TM) == 4) {
+      static_assert(mid_pair(FA[p]) == mid_pair(FB[p]) && mid_half(FB[p]) == 1, "layout pairs");
       const auto src = reinterpret_cast<gptr<const cpx<TM>>>(
-          mid + mid_pair(ORDER[i]) * pair_field(nx, NY) + (size_t)s * pair_strip_stride(NY) +
-          2 * mid_half(ORDER[i]));
-      if constexpr (FIRST_IN_REGS) {
-        fetch_strip_first<TM, NY, GR, NTHR, 2>(src, tid, cur);
-      } else {
-        fetch_strip<TM, NY, LPT, NTHR, 2>(src, tid, cur);
-      }
+                           mid + mid_pair(FA[p]) * pair_field(nx, NY) +
+                           st * pair_strip_stride(NY)) + (k & 1);
+      if constexpr (FIRST_IN_REGS)
+        fetch_strip_first<TM, NY, GR, NTHR, 2>(src, t, r);
+      else
+        fetch_strip<TM, NY, LPT, NTHR, 2>(src, t, r);
     } else {
-      fetch(ORDER[i], cur);
-    }
-    // field i's line (alternating buffers where GP::DBL)
-    cpx<TM>* ln = GP::DBL ? line + (i % 2) * NY : line;
-    if constexpr (sizeof(TM) == 8 || FRESH_SLOTS) {
-      // FP64 lines form their slots per transform as well: fewer registers
-      // held across the kernel, two workgroups per CU at N = 1024 and 2048
-      // (with FP32 lines in their own launch the extra address arithmetic
-      // costs more than the registers it frees).
-      const int tt = opaque_vgpr(tid);
-      const LS slt(tt);
-      column_dct2<TM, NY, LPT, UPT, NTHR, GR, MAP, FIRST_IN_REGS, !GP::DBL>(cur, ln, rt, slt, tt,
-                                                                          A, B);
-    } else {
-      column_dct2<TM, NY, LPT, UPT, NTHR, GR, MAP, FIRST_IN_REGS, !GP::DBL>(cur, ln, rt, sl, tid,
-                                                                          A, B);
-    }
-  };
-  // chi group: S~, H, Q~, K~ transformed and kept; their inner products are
-  // taken together with those of f_lin, bin by bin, so that each bin's
-  // weights 1/sigma are formed once.
-  auto keep_stage = [&](auto ia) {
-    constexpr int a = decltype(ia)::value;
-    TM A[KPT], B[KPT];
-    transform_next(ia, A, B);
+      const size_t o = st * strip_stride(NY, sizeof(TM)) + (k & 1);
+      const auto a = mid + FA[p] * strip_field(nx, NY, sizeof(TM)) + o;
+      const auto b = mid + FB[p] * strip_field(nx, NY, sizeof(TM)) + o;
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      if (S_LDS && a == 0) {
-        if (valid) keep[tid + j * KS] = {A[j], B[j]};
-      } else {
-        put(a, j, A[j], B[j]);
+      for (int q = 0; q < LPT; ++q) {
+        int row = t + q * NTHR;
+        if constexpr (FIRST_IN_REGS) row = row < NY / 2 ? 2 * row : 2 * (NY - 1 - row) + 1;
+        r.v[q] = (NY >= NTHR || row < NY) ? cpx<TM>{a[2 * row], b[2 * row]}
+                                          : cpx<TM>{(TM)0, (TM)0};
       }
     }
   };
-  keep_stage(std::integral_constant<int, 0>{});
-  keep_stage(std::integral_constant<int, 1>{});
-  keep_stage(std::integral_constant<int, 2>{});
-  keep_stage(std::integral_constant<int, 3>{});
+  constexpr bool AHEAD = GP::AHEAD && !FRESH_SLOTS;
+  StripRegs<TM, LPT> next;
+  if constexpr (AHEAD) fetch(std::integral_constant<int, 0>{}, tid, next);
+  auto transform = [&](auto ip, TM (&A)[KPT], TM (&B)[KPT]) {
+    constexpr int p = decltype(ip)::value;
+    constexpr bool FRESH = GP::FRESH || FRESH_SLOTS;
+    const int t = FRESH ? opaque_vgpr(tid) : tid;
+    StripRegs<TM, LPT> cur;
+    if constexpr (AHEAD) {
+      cur = next;
+      if constexpr (p < 3) fetch(std::integral_constant<int, p + 1>{}, t, next);
+    } else {
+      fetch(ip, t, cur);
+    }
+    cpx<TM>* ln = GP::DBL ? L.line + (p % 2) * NY : L.line;
+    if constexpr (FRESH) {
+      const LS slt(t);
+      column_dct2<TM, NY, LPT, UPT, NTHR, GR, MAP, FIRST_IN_REGS, !GP::DBL>(cur, ln, rt, slt, t,
+                                                                          A, B);
+    } else {
+      column_dct2<TM, NY, LPT, UPT, NTHR, GR, MAP, FIRST_IN_REGS, !GP::DBL>(cur, ln, rt, sl, t,
+                                                                          A, B);
+    }
+  };
+  double v[P2_NSUM];
+#pragma unroll
+  for (int q = 0; q < P2_NSUM; ++q) v[q] = 0.0;
+  // S~, H, Q~, K~ are kept; all chi products of a bin are formed together
+  // with f_lin, so that its weight 1/sigma is formed once.
+  constexpr bool KG = GP::KEEP_GLOBAL;
+  const auto kgs = kg + (size_t)k * 4 * NY + tid;
+  TM keep[4][KPT];
+  auto put = [&](int f, TM (&a)[KPT]) {
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) kgs[(f * KPT + j) * NTHR] = a[j];
+  };
+  transform(std::integral_constant<int, 0>{}, keep[0], keep[1]);
+  if constexpr (KG) {
+    put(0, keep[0]);
+    put(1, keep[1]);
+  }
+  transform(std::integral_constant<int, 1>{}, keep[2], keep[3]);
+  if constexpr (KG) {
+    put(2, keep[2]);
+    put(3, keep[3]);
+  }
+  TM f_hat[KPT], pg[KPT];         // f_lin; P~ (FP32) or g_lin (FP64)
+  transform(std::integral_constant<int, 2>{}, f_hat, pg);
   {
-    TM A[KPT], B[KPT];
-    transform_next(std::integral_constant<int, 4>{}, A, B);
     // pairs (x, y) of {S~, H, Q~, K~, f_lin} = indices 0..4
     constexpr int NPR = 14;
     constexpr int PX[NPR] = {0, 0, 0, 0, 1, 1, 1, 2, 2, 3, 4, 4, 4, 4};
     constexpr int PY[NPR] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3, 0, 1, 2, 3};
-    const int idx[NPR] = {P2_SS, P2_SH, P2_SQ, P2_SK, P2_HH, P2_HQ, P2_HK,
-                          P2_QQ, P2_QK, P2_KK, P2_FS, P2_FH, P2_FQ, P2_FK};
-    double v[NPR];
-#pragma unroll
-    for (int q = 0; q < NPR; ++q) v[q] = 0.0;
+    constexpr int IDX[NPR] = {P2_SS, P2_SH, P2_SQ, P2_SK, P2_HH, P2_HQ, P2_HK,
+                              P2_QQ, P2_QK, P2_KK, P2_FS, P2_FH, P2_FQ, P2_FK};
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
       if (!valid) continue;                  // blocks wider than half the line
-      double i0, i1;
-      inv_op(bin_of(j), true, i0, i1);
-      double xa[5], xb[5];
+      const double ev = lx + lamy[bin_of(j)];
+      const double w = rcp64(c.C1 + ev * (c.C2 + c.C3 * ev));
+      double x[5], wx[5];
 #pragma unroll
-      for (int f = 0; f < 4; ++f) {
-        TM ea, eb;
-        kept(f, j, ea, eb);
-        xa[f] = (double)ea;
-        xb[f] = (double)eb;
-      }
-      xa[4] = (double)A[j];
-      xb[4] = (double)B[j];
-      double wa[5], wb[5];
+      for (int f = 0; f < 4; ++f) x[f] = KG ? (double)kgs[(f * KPT + j) * NTHR] : (double)keep[f][j];
+      x[4] = (double)f_hat[j];
 #pragma unroll
-      for (int f = 0; f < 5; ++f) {
-        wa[f] = xa[f] * i0;
-        wb[f] = xb[f] * i1;
-      }
+      for (int f = 0; f < 5; ++f) wx[f] = x[f] * w;
 #pragma unroll
-      for (int q = 0; q < NPR; ++q) v[q] += wa[PX[q]] * xa[PY[q]] + wb[PX[q]] * xb[PY[q]];
+      for (int q = 0; q < NPR; ++q) v[IDX[q]] += wx[PX[q]] * x[PY[q]];
       __builtin_amdgcn_sched_barrier(0);
     }
-    accumulate(v, idx);
-  }
-  // zeta group: P~ and g_lin kept (in the H and Q~ slots), then L~; both
-  // inner products with one weight per bin.
-  if constexpr (KG) {
-    auto keep_zeta = [&](auto ii, int f) {
-      TM A[KPT], B[KPT];
-      transform_next(ii, A, B);
+    // formed before the next transform, not beside it (the kept spectra and
+    // the sums together exceed the registers)
 #pragma unroll
-      for (int j = 0; j < KPT; ++j) put(f, j, A[j], B[j]);
-    };
-    keep_zeta(std::integral_constant<int, 5>{}, 1);
-    keep_zeta(std::integral_constant<int, 6>{}, 2);
-  } else {
-    transform_next(std::integral_constant<int, 5>{}, ka[1], kb[1]);
-    transform_next(std::integral_constant<int, 6>{}, ka[2], kb[2]);
+    for (int q = 0; q < NPR; ++q) pin_vgpr(v[IDX[q]]);
   }
   {
+    // zeta: (P~, g_lin) and (P~, L~) with one weight per bin
     TM A[KPT], B[KPT];
-    transform_next(std::integral_constant<int, 7>{}, A, B);
-    double v[2] = {0.0, 0.0};
-    const int idx[2] = {P2_PG, P2_PL};
+    transform(std::integral_constant<int, 3>{}, A, B);
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
       if (!valid) continue;
-      double i0, i1;
-      inv_op(bin_of(j), false, i0, i1);
-      TM p0, p1, g0, g1;
-      kept(1, j, p0, p1);
-      kept(2, j, g0, g1);
-      const double pa = (double)p0 * i0, pb = (double)p1 * i1;
-      v[0] += pa * (double)g0 + pb * (double)g1;
-      v[1] += pa * (double)A[j] + pb * (double)B[j];
+      const double w = rcp64(c.alpha + c.lam * (lx + lamy[bin_of(j)]));
+      const double P = (double)(sizeof(TM) == 4 ? pg[j] : B[j]) * w;
+      v[P2_PG] += P * (double)(sizeof(TM) == 4 ? A[j] : pg[j]);
+      v[P2_PL] += P * (double)(sizeof(TM) == 4 ? B[j] : A[j]);
     }
-    accumulate(v, idx);
   }
-  if constexpr (ACC_LDS) {
-    // Sum the per-thread partials: thread t adds 16 consecutive threads'
-    // values of sum t / (NTHR / 16) (in a rotated order that keeps the lanes
-    // on different banks), then 16 threads add the chunks.
-    constexpr int CH = NTHR / 16;
-    lds_sync();
-    const int q = tid / CH, ch = tid % CH;
+  // The block's sums, through the line buffer (no longer read): each wave
+  // takes four sums at a time, 16 lanes adding four lanes' values each and
+  // then pairwise; the waves' totals are added in order.
+  const int lane = tid & 63, wave = tid >> 6;
+  double* buf = reinterpret_cast<double*>(L.line) + wave * 256;
+  lds_sync();
+#pragma unroll
+  for (int q0 = 0; q0 < P2_NSUM; q0 += 4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) buf[64 * i + lane] = v[q0 + i];
+    wave_lds_sync();
+    const double* b = buf + 64 * (lane >> 4) + 4 * (lane & 15);
+    double t = (b[0] + b[1]) + (b[2] + b[3]);
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off, 16);
+    if ((lane & 15) == 0) L.wsum[wave][q0 + (lane >> 4)] = t;
+    wave_lds_sync();
+  }
+  lds_sync();
+  if (tid < P2_NSUM) {
     double t = 0.0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) t += acc[q * NTHR + 16 * ch + ((i + ch) & 15)];
-    lds_sync();
-    acc[q * NTHR + ch] = t;
-    lds_sync();
-    if (tid < P2_NSUM) {
-      double u = 0.0;
-      for (int i = 0; i < CH; ++i) u += acc[tid * NTHR + i];
-      part[(size_t)s * P2_NSUM + tid] = u;
-    }
-  } else {
-    lds_sync();
-    if (tid < P2_NSUM) part[(size_t)s * P2_NSUM + tid] = acc[tid];
+    for (int w = 0; w < GP::WAVES; ++w) t += L.wsum[w][tid];
+    part[(size_t)k * P2_NSUM + tid] = t;
   }
 }
 
@@ -1665,10 +1488,10 @@ __device__ __forceinline__ void col_solve_body(gptr<const TM> __restrict__ mid,
         }
 #pragma unroll
         for (int q = 0; q < QC; ++q) {
-          ur[q0 + q] += w0 * (double)(h == 0 ? v[q][0] : v[q][2]);
-          ui[q0 + q] += w0 * (double)(h == 0 ? v[q][1] : v[q][3]);
+          ur[q0 + q] += w0 * (double)(h == 0 ? v[q][0] : v[q][1]);
+          ui[q0 + q] += w0 * (double)(h == 0 ? v[q][2] : v[q][3]);
           if (both) {
-            ur[q0 + q] += w1 * (double)v[q][2];
+            ur[q0 + q] += w1 * (double)v[q][1];
             ui[q0 + q] += w1 * (double)v[q][3];
           }
         }
@@ -2115,7 +1938,8 @@ __global__ void __launch_bounds__(line_threads(NX)) k_row_dct8(BATCH_PARAMS) {
 }
 
 template <typename TM, int NY>
-__global__ void __launch_bounds__(gram_threads<TM>(NY)) k_col_gram(BATCH_PARAMS) {
+__global__ void __launch_bounds__(gram_threads<TM>(NY), gram_waves(NY))
+k_col_gram(BATCH_PARAMS) {
   __shared__ GramLds<TM, NY> L;
   int blk;
   const MemberArgs& m = batch_member(tab, idx, per, blk);
