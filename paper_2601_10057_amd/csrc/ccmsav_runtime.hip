@@ -693,14 +693,13 @@ void enqueue_classical_solves(ccmsav_ctx* c, int table, hipStream_t st) {
 
 // The 5x5 kernel of `count` members of class k, with the thread count and
 // the slicing of their grid size (every path of a grid uses the same, so
-// results agree). Grids of 2048^2 cells and more reduce their thousands of
-// partial rows over SOLVE_SLICES workgroups each: measured on one MI355X,
-// 24.5 -> 15.0 us at N = 4096, 17.8 -> 14.2 us at N = 2048 and 48 -> 17 us
-// at N = 8192, while at N = 1024 one workgroup is faster (11.5 against
-// 12.8 us).
+// results agree). Grids of 1024^2 cells and more reduce their thousands of
+// partial rows over SOLVE_SLICES workgroups each: at N = 1024 11.5 us against
+// 14.5 us for one workgroup (at N = 512 one workgroup takes 10.4), at N =
+// 4096 13.6 us.
 void launch_solve(hipStream_t st, const SizeClass& k, int count, const MemberArgs* tab) {
   const size_t cells = (size_t)1 << (k.lx + k.ly);
-  if (cells >= (size_t)2048 * 2048)
+  if (cells >= (size_t)1024 * 1024)
     hipLaunchKernelGGL(k_solve_sliced<SOLVE_THREADS>, dim3(count * SOLVE_SLICES),
                        dim3(SOLVE_THREADS), 0, st, tab, k.d_idx, SOLVE_SLICES);
   else if (solve_threads(cells) == SOLVE_THREADS)

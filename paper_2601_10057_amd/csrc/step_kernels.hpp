@@ -1217,10 +1217,43 @@ constexpr int SOLVE_THREADS_SMALL = 256;
 inline int solve_threads(size_t cells) {
   return cells > (size_t)512 * 512 ? SOLVE_THREADS : SOLVE_THREADS_SMALL;
 }
-constexpr int SOLVE_NV_MAX = (int)P1_NSUM > (int)P2_NSUM ? (int)P1_NSUM : (int)P2_NSUM;
+static_assert((int)P1_NSUM == 16 && (int)P2_NSUM == 16, "rows of 16 sums in both passes");
 template <int NTHR> struct SolveLds {
-  double red[NTHR + SOLVE_NV_MAX];
+  double red[NTHR + 32];
 };
+
+// Column sums of the stencil's n1 and the Gram pass's n2 rows of partials:
+// red[NTHR + q] and red[NTHR + 16 + q]. The kernel is bound by the latency of
+// its loads, so half of the threads take each array, 16 to a row, with 32
+// loads in flight each (absent ones read as zero); the row groups' sums are
+// added in group order, a fixed order for any launch.
+template <int NTHR>
+__device__ __forceinline__ void solve_reduce(gptr<const double> __restrict__ p1, int n1,
+                                             gptr<const double> __restrict__ p2, int n2,
+                                             double* red, int tid) {
+  constexpr int H = NTHR / 2, G = H / 16, U = 32;
+  const bool second = tid >= H;
+  const auto p = second ? p2 : p1;
+  const int total = 16 * (second ? n2 : n1);
+  double v = 0.0;
+  for (int e = tid % H; e < total; e += U * H) {
+    double a[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = e + u * H < total ? p[e + u * H] : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) v += a[u];
+  }
+  red[tid] = v;
+  lds_sync();
+  if (tid < 32) {
+    const double* r = red + (tid >> 4) * H + (tid & 15);
+    double t = 0.0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) t += r[g * 16];
+    red[NTHR + tid] = t;
+  }
+  lds_sync();
+}
 
 // The 5x5 system from the reduced sums T1 (stencil pass) and T2 (column
 // pass), its solution, the new SAVs and the combination coefficients; run by
@@ -1356,11 +1389,15 @@ __device__ __forceinline__ void solve_body(gptr<const double> __restrict__ p1, i
                                            gptr<const double> __restrict__ p2, int n2,
                                            gptr<DevScalars> __restrict__ ds, const StepConst& c,
                                            SolveLds<NTHR>& L, int tid) {
-  double* red = L.red;
+  solve_reduce<NTHR>(p1, n1, p2, n2, L.red, tid);
+  if (tid != 0) return;
   double T1[P1_NSUM], T2[P2_NSUM];
-  reduce_columns<P1_NSUM, NTHR>(p1, n1, red, tid, T1);
-  reduce_columns<P2_NSUM, NTHR>(p2, n2, red, tid, T2);
-  if (tid == 0) solve_system(T1, T2, ds, c);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    T1[q] = L.red[NTHR + q];
+    T2[q] = L.red[NTHR + 16 + q];
+  }
+  solve_system(T1, T2, ds, c);
 }
 
 // SOLVE_SLICES workgroups per grid: workgroup g reduces slice g of the
@@ -1377,7 +1414,6 @@ __device__ __forceinline__ void solve_sliced_body(gptr<const double> __restrict_
                                                   gptr<DevScalars> __restrict__ ds,
                                                   const StepConst& c, int g, SolveLds<NTHR>& L,
                                                   int tid) {
-  static_assert(NTHR >= P1_NSUM + P2_NSUM, "one thread per sum for the slice totals");
   double* red = L.red;
   __shared__ int last;
   {
@@ -1385,14 +1421,12 @@ __device__ __forceinline__ void solve_sliced_body(gptr<const double> __restrict_
     const int b1 = (int)((long long)n1 * (g + 1) / SOLVE_SLICES);
     const int a2 = (int)((long long)n2 * g / SOLVE_SLICES);
     const int b2 = (int)((long long)n2 * (g + 1) / SOLVE_SLICES);
-    double T1[P1_NSUM], T2[P2_NSUM];
-    reduce_columns<P1_NSUM, NTHR>(p1 + (size_t)a1 * P1_NSUM, b1 - a1, red, tid, T1);
-    reduce_columns<P2_NSUM, NTHR>(p2 + (size_t)a2 * P2_NSUM, b2 - a2, red, tid, T2);
+    solve_reduce<NTHR>(p1 + (size_t)a1 * P1_NSUM, b1 - a1, p2 + (size_t)a2 * P2_NSUM, b2 - a2,
+                       red, tid);
+    // (the slice's 32 threads and thread 0 are one wave: its release fence
+    // covers their stores)
+    if (tid < P1_NSUM + P2_NSUM) ds->slice[g][tid] = red[NTHR + tid];
     if (tid == 0) {
-#pragma unroll
-      for (int q = 0; q < P1_NSUM; ++q) ds->slice[g][q] = T1[q];
-#pragma unroll
-      for (int q = 0; q < P2_NSUM; ++q) ds->slice[g][P1_NSUM + q] = T2[q];
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       const unsigned done = __hip_atomic_fetch_add(&ds->slices_done, 1u, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT);
@@ -1404,6 +1438,7 @@ __device__ __forceinline__ void solve_sliced_body(gptr<const double> __restrict_
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   if (tid < P1_NSUM + P2_NSUM) {
     double t = 0.0;
+#pragma unroll
     for (int h = 0; h < SOLVE_SLICES; ++h) t += ds->slice[h][tid];
     red[tid] = t;
   }
