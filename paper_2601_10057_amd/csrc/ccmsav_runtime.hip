@@ -920,8 +920,7 @@ int enqueue_step_gemm(ccmsav_ctx* c, int64_t level, hipStream_t st, PhaseEvents 
   return CCMSAV_OK;
 }
 
-int periodic_solve_pc(const Member& m, int precision, hipStream_t st, const double* rhs,
-                      double* out_chi, double* out_zeta, const PerConst& pc);
+void periodic_step_solves(const Member& m, hipStream_t st, const PerConst& pc);
 
 // One step of the single member with periodic boundaries (FP64): the stencil
 // pass with wrap-around ghosts, the seven elliptic solves of Algorithm 1 by
@@ -937,22 +936,12 @@ int enqueue_step_periodic(ccmsav_ctx* c, int64_t level, hipStream_t st, PhaseEve
   const int nx = m.p.nx, ny = m.p.ny;
   const size_t cells = (size_t)nx * ny;
   double* rm = static_cast<double*>(m.rm);
-  auto field = [&](int f) { return rm + (size_t)f * cells; };
   const PerConst pc{sc.C1, sc.C2, sc.C3, sc.alpha, sc.lam, m.p.h};
   pe.mark(0, st);
   launch_stencil<double>(c, k, tab, st);
   pe.mark(1, st);
   pe.mark(2, st);
-  int r = periodic_solve_pc(m, c->precision, st, field(M_F), field(M_F), nullptr, pc);
-  const int chi_src[4] = {M_S, M_H, M_Q, M_K};
-  for (int i = 0; i < 4 && r == CCMSAV_OK; ++i)
-    r = periodic_solve_pc(m, c->precision, st, field(chi_src[i]), m.psol + (size_t)i * cells,
-                          nullptr, pc);
-  if (r == CCMSAV_OK)
-    r = periodic_solve_pc(m, c->precision, st, field(M_G), nullptr, field(M_G), pc);
-  if (r == CCMSAV_OK)
-    r = periodic_solve_pc(m, c->precision, st, field(M_L), nullptr, field(M_L), pc);
-  if (r != CCMSAV_OK) return r;
+  periodic_step_solves(m, st, pc);
   pe.mark(3, st);
   pe.mark(4, st);
   hipLaunchKernelGGL(k_per_gram, dim3(ny), dim3(PER_THREADS), 0, st, rm, m.psol, m.part2, nx, ny);
@@ -1310,29 +1299,25 @@ const char* kStatusText[] = {
 
 namespace {
 
-// Launches of the periodic solver over the line length (16 .. 4096).
+// Launches of the periodic solver over the line length (16 .. 4096), `nf`
+// fields each.
 constexpr int kPerMaxLog = 12;
 struct PerLaunch {
-  using Rows = void (*)(hipStream_t, int, const double*, cpx<double>*, int, size_t);
-  using Cols = void (*)(hipStream_t, int, const cpx<double>*, cpx<double>*, cpx<double>*, int,
-                        size_t, PerConst);
-  using Inv = void (*)(hipStream_t, int, const cpx<double>*, double*, int, size_t);
+  using Rows = void (*)(hipStream_t, int, int, const PerRows&, int, size_t);
+  using Cols = void (*)(hipStream_t, int, int, const PerCols&, int, size_t, PerConst);
+  using Inv = void (*)(hipStream_t, int, int, const PerInv&, int, size_t);
   template <int N>
-  static void rows(hipStream_t st, int grid, const double* rhs, cpx<double>* col, int ny,
-                   size_t cs) {
-    hipLaunchKernelGGL(k_per_rows<N>, dim3(grid), dim3(line_threads(N)), 0, st, rhs, col, ny, cs);
+  static void rows(hipStream_t st, int grid, int nf, const PerRows& f, int ny, size_t cs) {
+    hipLaunchKernelGGL(k_per_rows<N>, dim3(grid, nf), dim3(line_threads(N)), 0, st, f, ny, cs);
   }
   template <int N>
-  static void cols(hipStream_t st, int grid, const cpx<double>* col, cpx<double>* oc,
-                   cpx<double>* oz, int nx, size_t cs, PerConst k) {
-    hipLaunchKernelGGL(k_per_cols<N>, dim3(grid), dim3(line_threads(N)), 0, st, col, oc, oz, nx,
-                       cs, k);
+  static void cols(hipStream_t st, int grid, int nf, const PerCols& f, int nx, size_t cs,
+                   PerConst k) {
+    hipLaunchKernelGGL(k_per_cols<N>, dim3(grid, nf), dim3(line_threads(N)), 0, st, f, nx, cs, k);
   }
   template <int N>
-  static void inv(hipStream_t st, int grid, const cpx<double>* col, double* out, int ny,
-                  size_t cs) {
-    hipLaunchKernelGGL(k_per_rows_inv<N>, dim3(grid), dim3(line_threads(N)), 0, st, col, out, ny,
-                       cs);
+  static void inv(hipStream_t st, int grid, int nf, const PerInv& f, int ny, size_t cs) {
+    hipLaunchKernelGGL(k_per_rows_inv<N>, dim3(grid, nf), dim3(line_threads(N)), 0, st, f, ny, cs);
   }
   template <int... L> struct Tables {
     static constexpr Rows t_rows[] = {&rows<(1 << L)>...};
@@ -1342,37 +1327,71 @@ struct PerLaunch {
   using T = Tables<4, 5, 6, 7, 8, 9, 10, 11, 12>;
 };
 
-// Periodic chi^{-1} rhs and zeta^{-1} rhs of member m (FP64 transforms) with
-// the operator constants pc, on stream st, with three column buffers of
-// (nx/2 + 1) columns in the member's intermediate region. An output may be
-// rhs itself (the row pass has read rhs before the inverse rows write).
-int periodic_solve_pc(const Member& m, int precision, hipStream_t st, const double* rhs,
-                      double* out_chi, double* out_zeta, const PerConst& pc) {
+// Column buffers of the periodic solver: nx/2 + 1 columns of ny complex
+// values at a stride off a power of two, in the intermediate region.
+size_t per_col_stride(int ny) { return (size_t)ny + 66; }
+size_t per_col_buffer(int nx, int ny) { return (size_t)(nx / 2 + 1) * per_col_stride(ny); }
+
+// The standalone periodic solve of member 0 with the BDF2 operators (FP64
+// transforms in any precision). An output may be rhs itself (the row pass has
+// read rhs before the inverse rows write).
+int periodic_solve(ccmsav_ctx* c, const double* rhs, double* out_chi, double* out_zeta) {
+  const Member& m = c->mem[0];
+  const StepConst& k = c->h_args[(size_t)kSolveTable * c->mem.size()].k;
+  const PerConst pc{k.C1, k.C2, k.C3, k.alpha, k.lam, m.p.h};
   const int nx = m.p.nx, ny = m.p.ny;
   if (m.lx > kPerMaxLog || m.ly > kPerMaxLog) return CCMSAV_EUNSUPPORTED;
-  const size_t cs = (size_t)ny + 66;             // column stride, off a power of two
-  const size_t colb = (size_t)(nx / 2 + 1) * cs;
+  const size_t cs = per_col_stride(ny), colb = per_col_buffer(nx, ny);
   const size_t need = 3 * colb * sizeof(cpx<double>);
-  const size_t have = M_NFIELD * strip_field(nx, ny, (int)mid_elem(precision)) *
-                      mid_elem(precision);
+  const size_t have = M_NFIELD * strip_field(nx, ny, (int)mid_elem(c->precision)) *
+                      mid_elem(c->precision);
   if (need > have) return CCMSAV_EUNSUPPORTED;
   cpx<double>* col = static_cast<cpx<double>*>(m.mid);
-  cpx<double>* cc = col + colb;
-  cpx<double>* cz = cc + colb;
   using PT = PerLaunch::T;
-  PT::t_rows[m.lx - kMinLog](st, ny / 2, rhs, col, ny, cs);
-  PT::t_cols[m.ly - kMinLog](st, nx / 2 + 1, col, out_chi ? cc : nullptr,
-                             out_zeta ? cz : nullptr, nx, cs, pc);
-  if (out_chi) PT::t_inv[m.lx - kMinLog](st, ny / 2, cc, out_chi, ny, cs);
-  if (out_zeta) PT::t_inv[m.lx - kMinLog](st, ny / 2, cz, out_zeta, ny, cs);
+  PerRows rows{{rhs}, col, colb};
+  PerCols cols{{col}, {out_chi ? col + colb : nullptr}, {out_zeta ? col + 2 * colb : nullptr}};
+  PerInv inv{};
+  int ni = 0;
+  auto add = [&](const cpx<double>* from, double* to) {
+    if (!to) return;
+    inv.col[ni] = from;
+    inv.dst[ni++] = to;
+  };
+  add(col + colb, out_chi);
+  add(col + 2 * colb, out_zeta);
+  PT::t_rows[m.lx - kMinLog](c->stream, ny / 2, 1, rows, ny, cs);
+  PT::t_cols[m.ly - kMinLog](c->stream, nx / 2 + 1, 1, cols, nx, cs, pc);
+  if (ni > 0) PT::t_inv[m.lx - kMinLog](c->stream, ny / 2, ni, inv, ny, cs);
   return hipGetLastError() == hipSuccess ? CCMSAV_OK : CCMSAV_EHIP;
 }
 
-// The standalone periodic solve of member 0 with the BDF2 operators.
-int periodic_solve(ccmsav_ctx* c, const double* rhs, double* out_chi, double* out_zeta) {
-  const StepConst& k = c->h_args[(size_t)kSolveTable * c->mem.size()].k;
-  const PerConst pc{k.C1, k.C2, k.C3, k.alpha, k.lam, c->mem[0].p.h};
-  return periodic_solve_pc(c->mem[0], c->precision, c->stream, rhs, out_chi, out_zeta, pc);
+// The seven solves of a periodic step, FP64: chi^{-1} of f_lin (in place), S~,
+// H, Q~, K~ (into psol), zeta^{-1} of g_lin and L~ (in place). Seven column
+// buffers take at most 7 (nx/2 + 1) columns of the 8 nx/2 in the intermediate
+// region (nx >= 16).
+void periodic_step_solves(const Member& m, hipStream_t st, const PerConst& pc) {
+  const int nx = m.p.nx, ny = m.p.ny;
+  const size_t cells = (size_t)nx * ny;
+  const size_t cs = per_col_stride(ny), colb = per_col_buffer(nx, ny);
+  cpx<double>* col = static_cast<cpx<double>*>(m.mid);
+  double* rm = static_cast<double*>(m.rm);
+  const int slot[PER_FIELDS] = {M_F, M_S, M_H, M_Q, M_K, M_G, M_L};
+  PerRows rows{{}, col, colb};
+  PerCols cols{};
+  PerInv inv{};
+  for (int f = 0; f < PER_FIELDS; ++f) {
+    double* field = rm + (size_t)slot[f] * cells;
+    const bool chi = f < 5;
+    rows.src[f] = field;
+    cols.col[f] = col + f * colb;
+    (chi ? cols.chi : cols.zeta)[f] = col + f * colb;
+    inv.col[f] = col + f * colb;
+    inv.dst[f] = f >= 1 && f <= 4 ? m.psol + (size_t)(f - 1) * cells : field;
+  }
+  using PT = PerLaunch::T;
+  PT::t_rows[m.lx - kMinLog](st, ny / 2, PER_FIELDS, rows, ny, cs);
+  PT::t_cols[m.ly - kMinLog](st, nx / 2 + 1, PER_FIELDS, cols, nx, cs, pc);
+  PT::t_inv[m.lx - kMinLog](st, ny / 2, PER_FIELDS, inv, ny, cs);
 }
 
 // Upload `a` (a copy of the standalone-solve table entry, with the operator

@@ -20,9 +20,28 @@ template <int N> __device__ __forceinline__ int per_slot(int k) {
   return LdsMap<double, N, SWZ_LINE>::at(digit_rev<N, 8>(k));
 }
 
+// Fields of one launch: blockIdx.y picks the field. A step's seven solves go
+// through the three kernels together: at N = 512 one field's launch is a
+// fraction of the device (256 to 513 workgroups of two waves, 5 to 9 us each,
+// 137 us for 21 of them; together about 40 us).
+constexpr int PER_FIELDS = 7;
+struct PerRows {
+  const double* src[PER_FIELDS];       // real fields, row-major
+  cpx<double>* col;                    // their half spectra, one buffer after another
+  size_t stride;                       // elements of one buffer
+};
+struct PerCols {
+  const cpx<double>* col[PER_FIELDS];  // half spectra along x
+  cpx<double>* chi[PER_FIELDS];        // chi^{-1} and zeta^{-1} of them (null to
+  cpx<double>* zeta[PER_FIELDS];       //   skip); may be the input
+};
+struct PerInv {
+  const cpx<double>* col[PER_FIELDS];
+  double* dst[PER_FIELDS];
+};
+
 template <int NX>
-__global__ void __launch_bounds__(line_threads(NX))
-k_per_rows(const double* __restrict__ rhs, cpx<double>* __restrict__ col, int ny, size_t cs) {
+__global__ void __launch_bounds__(line_threads(NX)) k_per_rows(PerRows f, int ny, size_t cs) {
   constexpr int NTHR = line_threads(NX);
   using MAP = LdsMap<double, NX, SWZ_LINE>;
   __shared__ cpx<double> line[NX];
@@ -30,6 +49,8 @@ k_per_rows(const double* __restrict__ rhs, cpx<double>* __restrict__ col, int ny
   const int tid = threadIdx.x;
   const int j = 2 * blockIdx.x;
   if (j + 1 >= ny) return;                       // whole workgroup: no barrier skipped
+  const double* __restrict__ rhs = f.src[blockIdx.y];
+  cpx<double>* __restrict__ col = f.col + blockIdx.y * f.stride;
   Roots<double, NX> rt;
   rt.init(rtab, tid, NTHR);
   for (int i = tid; i < NX; i += NTHR)
@@ -58,8 +79,7 @@ struct PerConst {
 
 template <int NY>
 __global__ void __launch_bounds__(line_threads(NY))
-k_per_cols(const cpx<double>* __restrict__ col, cpx<double>* __restrict__ out_chi,
-           cpx<double>* __restrict__ out_zeta, int nx, size_t cs, PerConst c) {
+k_per_cols(PerCols f, int nx, size_t cs, PerConst c) {
   constexpr int NTHR = line_threads(NY);
   using MAP = LdsMap<double, NY, SWZ_LINE>;
   __shared__ cpx<double> a[NY];
@@ -68,23 +88,25 @@ k_per_cols(const cpx<double>* __restrict__ col, cpx<double>* __restrict__ out_ch
   const int tid = threadIdx.x;
   const int kx = blockIdx.x;
   if (kx > nx / 2) return;                       // whole workgroup
+  const cpx<double>* col = f.col[blockIdx.y];
   Roots<double, NY> rt;
   rt.init(rtab, tid, NTHR);
   const size_t base = (size_t)kx * cs;
   for (int i = tid; i < NY; i += NTHR) a[MAP::at(i)] = col[base + i];
   lds_sync();
   fft_lines<double, NY, 1, NTHR, 8, MAP>(a, rt, tid);
+  const double h4 = 4.0 / (c.h * c.h);
   const double sx = sinpi((double)kx / nx);
-  const double lx = 4.0 / (c.h * c.h) * sx * sx;
+  const double lx = h4 * sx * sx;
   for (int op = 0; op < 2; ++op) {
-    cpx<double>* out = op == 0 ? out_chi : out_zeta;
+    cpx<double>* out = op == 0 ? f.chi[blockIdx.y] : f.zeta[blockIdx.y];
     if (!out) continue;                          // uniform over the workgroup
     for (int k = tid; k < NY; k += NTHR) {
-      const double sy = sinpi((double)k / NY);
-      const double L = lx + 4.0 / (c.h * c.h) * sy * sy;
-      const double s = op == 0 ? c.C1 + L * (c.C2 + c.C3 * L) : c.alpha + c.lam * L;
+      const double sy = rt.omega64(2 * k).im;    // -sin(pi k / ny)
+      const double L = lx + h4 * sy * sy;
+      const double s = rcp64(op == 0 ? c.C1 + L * (c.C2 + c.C3 * L) : c.alpha + c.lam * L);
       const cpx<double> x = a[per_slot<NY>(k)];
-      b[MAP::at(k)] = {x.re / s, -x.im / s};     // conjugate of X / s
+      b[MAP::at(k)] = {x.re * s, -x.im * s};     // conjugate of X / s
     }
     lds_sync();
     fft_lines<double, NY, 1, NTHR, 8, MAP>(b, rt, tid);
@@ -97,8 +119,7 @@ k_per_cols(const cpx<double>* __restrict__ col, cpx<double>* __restrict__ out_ch
 }
 
 template <int NX>
-__global__ void __launch_bounds__(line_threads(NX))
-k_per_rows_inv(const cpx<double>* __restrict__ col, double* __restrict__ out, int ny, size_t cs) {
+__global__ void __launch_bounds__(line_threads(NX)) k_per_rows_inv(PerInv f, int ny, size_t cs) {
   constexpr int NTHR = line_threads(NX);
   using MAP = LdsMap<double, NX, SWZ_LINE>;
   __shared__ cpx<double> line[NX];
@@ -106,6 +127,8 @@ k_per_rows_inv(const cpx<double>* __restrict__ col, double* __restrict__ out, in
   const int tid = threadIdx.x;
   const int j = 2 * blockIdx.x;
   if (j + 1 >= ny) return;                       // whole workgroup
+  const cpx<double>* __restrict__ col = f.col[blockIdx.y];
+  double* __restrict__ out = f.dst[blockIdx.y];
   Roots<double, NX> rt;
   rt.init(rtab, tid, NTHR);
   for (int k = tid; k <= NX / 2; k += NTHR) {
@@ -126,9 +149,9 @@ k_per_rows_inv(const cpx<double>* __restrict__ col, double* __restrict__ out, in
 
 // ---------------------------------------------------------------------------
 // The time step with periodic boundaries (FP64). Algorithm 1 of App. B with
-// the seven elliptic solves done by the solver above: chi^{-1} of f_lin (in
-// place) and of S~, H, Q~, K~ (into four fields of their own), zeta^{-1} of
-// g_lin and L~ (in place). The inner products of App. B Step 4 are then taken
+// the seven elliptic solves done by the solver above, in one launch of each of
+// its kernels: chi^{-1} of f_lin (in place) and of S~, H, Q~, K~ (into four
+// fields of their own), zeta^{-1} of g_lin and L~ (in place). The inner products of App. B Step 4 are then taken
 // in physical space and the solution combined from the solved fields.
 // ---------------------------------------------------------------------------
 constexpr int PER_THREADS = 256;
