@@ -206,7 +206,7 @@ Layout layout(const ccmsav_params* p) {
   if (is_classical(p)) {
     // x, r, p (two buffers), q, z for both systems, and the two face mobilities
     L.cl = off;     off = align_up(off + 14 * cells * sizeof(double));
-    L.clpart = off; off = align_up(off + (size_t)CL_BLOCKS * CL_NSUM * sizeof(double));
+    L.clpart = off; off = align_up(off + (size_t)CL_MAX_BLOCKS * CL_PART_SUMS * sizeof(double));
     L.clsc = off;   off = align_up(off + sizeof(PcgScalars));
   }
   L.total = off;
@@ -629,13 +629,49 @@ void run_tuned(ccmsav_ctx* c, Tuner& tu, size_t ki, int t, hipStream_t st, F lau
     }
 }
 
+// Launches of the classical scheme's row kernels over the line length, one
+// workgroup per grid row.
+struct ClRowArgs {
+  const double* b;
+  double* x;
+  double* r;
+  const double* q;
+  double* mid;
+  const double* out;
+  double* z;
+  int ny;
+  ClPart part;
+  int pq_rows;
+  PcgScalars* sc;
+};
+struct ClLaunch {
+  using Update = void (*)(hipStream_t, const double*, const ClRowArgs&, int);
+  using Inv = void (*)(hipStream_t, const ClRowArgs&);
+  template <int N, bool INIT>
+  static void update(hipStream_t st, const double* p, const ClRowArgs& a, int it) {
+    hipLaunchKernelGGL((k_cl_update_rows<N, INIT>), dim3(a.ny), dim3(line_threads(N)), 0, st, a.b,
+                       a.x, a.r, p, a.q, a.mid, a.ny, a.part, a.pq_rows, a.sc, it);
+  }
+  template <int N, bool INIT> static void inv(hipStream_t st, const ClRowArgs& a) {
+    hipLaunchKernelGGL((k_cl_inv_rows<N, INIT>), dim3(a.ny), dim3(line_threads(N)), 0, st, a.out,
+                       a.r, a.z, a.ny, a.part, a.sc);
+  }
+  template <int... L> struct Tables {
+    static constexpr Update t_update[2][sizeof...(L)] = {{&update<(1 << L), false>...},
+                                                         {&update<(1 << L), true>...}};
+    static constexpr Inv t_inv[2][sizeof...(L)] = {{&inv<(1 << L), false>...},
+                                                   {&inv<(1 << L), true>...}};
+  };
+  using T = Tables<4, 5, 6, 7, 8, 9, 10, 11, 12, 13>;
+};
+
 // The classical scheme's two variable-coefficient solves of one step (FP64,
 // one member), after the stencil pass has written g_lin (with lambda
 // div(M grad psi*)), L~, P~ and the face mobilities: the preconditioner's
-// constants, x = 0, r = b, z = P^{-1} r, then pcg_max_iter iterations of
-// {p = z + beta p, q = zeta p; a; x += a p, r -= a q; stop test; z = P^{-1} r;
-// (r, z), beta}, whose kernels return at once once both systems have met the
-// tolerance, and the inner products (P~, x_s) with the mean correction. The
+// constants, x = 0, r = b, z = P^{-1} r, then pcg_max_iter iterations of four
+// kernels (classical_kernels.hpp), which return at once once both systems have
+// met the tolerance, and the inner products (P~, x_s) with the mean
+// correction. The
 // intermediate fields serve as the preconditioner's scratch before the row
 // DCT of the step overwrites them.
 void enqueue_classical_solves(ccmsav_ctx* c, int table, hipStream_t st) {
@@ -646,49 +682,40 @@ void enqueue_classical_solves(ccmsav_ctx* c, int table, hipStream_t st) {
   const MemberArgs* pre = c->d_args + (size_t)kPcgTable * c->mem.size();
   const StepConst& sc = c->h_args[(size_t)table * c->mem.size()].k;
   double* rm = static_cast<double*>(m.rm);
+  double* mid = static_cast<double*>(m.mid);
   const double* b = rm + (size_t)M_G * n;          // g_lin and L~ are consecutive slots
-  const int rows = CL_BLOCKS;
   using LT = Launch<double>::T;
-  auto precondition = [&]() {
-    LT::t_rd[m.lx - kMinLog](st, ny, m.cl_r, static_cast<double*>(m.mid), M_F, ny,
-                             &m.cl_sc->done_all);
-    LT::t_rd[m.lx - kMinLog](st, ny, m.cl_r + n, static_cast<double*>(m.mid), M_G, ny,
-                             &m.cl_sc->done_all);
+  const int units = (nx + 63) / 64 * (ny / CL_ROWS);
+  const int mv_blocks = std::min((units + CL_THREADS / 64 - 1) / (CL_THREADS / 64), 2 * CL_BLOCKS);
+  double* const pt = m.cl_part;
+  const ClPart part{pt, pt + 2 * CL_MAX_BLOCKS, pt + 4 * CL_MAX_BLOCKS, pt + 6 * CL_MAX_BLOCKS};
+  const ClRowArgs rows{b,   m.cl_x, m.cl_r, m.cl_q,    mid,    static_cast<const double*>(m.outc),
+                       m.cl_z, ny,  part,   mv_blocks, m.cl_sc};
+  const int lx = m.lx - kMinLog;
+  // z = P^{-1} r from the row-transformed residuals
+  auto precondition = [&](int init) {
     LT::t_col_solve[k.var[TUNE_COL_SOLVE]][m.ly - kMinLog](st, nx, Batch{pre, k.d_idx, nx});
-    const int vi = k.var[TUNE_ROW_IDCT];
-    const int per = ny / row_idct_rows<double>(nx, vi);
-    LT::t_row_idct[vi][m.lx - kMinLog](st, per, Batch{pre, k.d_idx, per});
-    hipLaunchKernelGGL(k_cl_dot_rz, dim3(CL_BLOCKS), dim3(CL_THREADS), 0, st, m.cl_r, m.cl_z,
-                       m.cl_part, n, m.cl_sc);
-    hipLaunchKernelGGL(k_cl_scalars<CL_RZ>, dim3(1), dim3(512), 0, st, m.cl_part, rows, m.cl_sc,
-                       m.ds, (double)n, 0);
+    ClLaunch::T::t_inv[init][lx](st, rows);
   };
   hipLaunchKernelGGL(k_cl_setup, dim3(1), dim3(512), 0, st, m.part1, m.sh.units,
                      const_cast<MemberArgs*>(pre), m.cl_sc, sc.alpha, m.p.lam, c->pcg_tol,
                      (double)n);
-  hipLaunchKernelGGL(k_cl_start, dim3(CL_BLOCKS), dim3(CL_THREADS), 0, st, b, m.cl_x, m.cl_r,
-                     m.cl_part, n, m.cl_sc);
-  hipLaunchKernelGGL(k_cl_scalars<CL_INIT>, dim3(1), dim3(512), 0, st, m.cl_part, rows, m.cl_sc,
-                     m.ds, (double)n, 0);
-  precondition();
+  ClLaunch::T::t_update[1][lx](st, nullptr, rows, 0);
+  precondition(1);
   for (int it = 0; it < c->pcg_max_iter; ++it) {
     double* p_old = m.cl_p[it & 1];
     double* p_new = m.cl_p[(it + 1) & 1];
-    hipLaunchKernelGGL(k_cl_matvec, dim3(CL_BLOCKS), dim3(CL_THREADS), 0, st, m.cl_z, p_old,
-                       p_new, m.cl_q, m.mob_e, m.mob_n, nx, ny, 1.0 / (m.p.h * m.p.h), m.cl_part,
-                       m.cl_sc);
-    hipLaunchKernelGGL(k_cl_scalars<CL_PQ>, dim3(1), dim3(512), 0, st, m.cl_part, rows, m.cl_sc,
-                       m.ds, (double)n, 0);
-    hipLaunchKernelGGL(k_cl_update, dim3(CL_BLOCKS), dim3(CL_THREADS), 0, st, m.cl_x, m.cl_r,
-                       p_new, m.cl_q, m.cl_part, n, m.cl_sc);
-    hipLaunchKernelGGL(k_cl_scalars<CL_RR>, dim3(1), dim3(512), 0, st, m.cl_part, rows, m.cl_sc,
-                       m.ds, (double)n, it + 1 == c->pcg_max_iter ? 1 : 0);
-    if (it + 1 < c->pcg_max_iter) precondition();
+    hipLaunchKernelGGL(k_cl_matvec, dim3(mv_blocks), dim3(CL_THREADS), 0, st, m.cl_z, p_old,
+                       p_new, m.cl_q, m.mob_e, m.mob_n, nx, ny, 1.0 / (m.p.h * m.p.h), part,
+                       m.cl_sc, it);
+    ClLaunch::T::t_update[0][lx](st, p_new, rows, it);
+    if (it + 1 < c->pcg_max_iter) precondition(0);
   }
+  hipLaunchKernelGGL(k_cl_last, dim3(1), dim3(CL_THREADS), 0, st, part, ny, m.cl_sc, m.ds);
   hipLaunchKernelGGL(k_cl_gram, dim3(CL_BLOCKS), dim3(CL_THREADS), 0, st,
-                     rm + (size_t)M_P * n, m.cl_x, m.cl_part, n);
-  hipLaunchKernelGGL(k_cl_scalars<CL_FINAL>, dim3(1), dim3(512), 0, st, m.cl_part, rows, m.cl_sc,
-                     m.ds, (double)n, 0);
+                     rm + (size_t)M_P * n, m.cl_x, part, n);
+  hipLaunchKernelGGL(k_cl_final, dim3(1), dim3(CL_THREADS), 0, st, part, CL_BLOCKS, m.cl_sc,
+                     m.ds, (double)n);
 }
 
 // The 5x5 kernel of `count` members of class k, with the thread count and

@@ -840,6 +840,34 @@ __device__ __forceinline__ void row_dct8_body(gptr<const TM> __restrict__ rm,
   }
 }
 
+// Post-processing of a transformed row line (two real rows or fields as one
+// complex line) by column pairs: store(sp, A_2sp, A_2sp+1, B_2sp, B_2sp+1).
+// The slots of bins 2 sp, 2 sp + 1 and their mirrors as in row_dct8_body.
+template <typename TM, int NX, int NTHR, typename MAP, typename F>
+__device__ __forceinline__ void row_dct_pairs(const cpx<TM>* line, const Roots<TM, NX>& rt,
+                                              int tid, F&& store) {
+  using LS = LineSlots<NX, NTHR, fft_radix<TM>(), MAP>;
+  constexpr int SPT = NX / 2 >= NTHR ? NX / 2 / NTHR : 1;
+  const TM S0 = (TM)(0.5 * sqrt(1.0 / NX)), S1 = (TM)(0.5 * sqrt(2.0 / NX));
+  const int g2 = LS::g(2 * tid);
+  const int g2m = MAP::at(NX - 1) ^ LS::g(1) ^ LS::g((2 * tid - 2) & (NX - 1));
+#pragma unroll
+  for (int it = 0; it < SPT; ++it) {
+    const int sp = tid + it * NTHR;
+    if (NX / 2 >= NTHR || sp < NX / 2) {
+      const int pk0 = g2 ^ LS::g(2 * it * NTHR), pk1 = pk0 ^ LS::g(1);
+      const int pm1 = pk0 ^ MAP::at(NX - 1);
+      const int pm0 = tid == 0 ? (it == 0 ? 0 : (MAP::at(NX - 1) ^ LS::g(1) ^
+                                                 LS::g((2 * it * NTHR - 2) & (NX - 1))))
+                               : (g2m ^ LS::g(2 * it * NTHR));
+      TM a0, a1, b0, b1;
+      dct2_bin<TM>(line[pk0], line[pm0], rt.omega(2 * sp), sp == 0 ? S0 : S1, a0, b0);
+      dct2_bin<TM>(line[pk1], line[pm1], rt.omega(2 * sp + 1), S1, a1, b1);
+      store(sp, a0, a1, b0, b1);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // P2: column DCT-II of the eight fields and the spectral Gram sums.
 // ---------------------------------------------------------------------------
