@@ -26,6 +26,7 @@
 #include "persist_kernels.hpp"
 #include "periodic_kernels.hpp"
 #include "smooth_kernels.hpp"
+#include "solve_kernels.hpp"
 #include "step_kernels.hpp"
 
 using namespace ccm;
@@ -38,11 +39,10 @@ constexpr size_t kAlign = 256;
 constexpr int kNumPhases = 6;   // stencil, row DCT, column Gram, 5x5 solve, column solve, row IDCT
 constexpr int kMaxMembers = 4096;
 // Argument tables: 0 = level 0 (BDF1), 1 = level 1 (first BDF2 step, no
-// lagged ||d||^2), 2 + r = level n >= 2 with n % 3 == r; 5 = standalone solve;
-// 6 = the classical scheme's preconditioner solve.
-constexpr int kNumTables = 7;
-constexpr int kSolveTable = 5;
-constexpr int kPcgTable = 6;
+// lagged ||d||^2), 2 + r = level n >= 2 with n % 3 == r; 5 = the classical
+// scheme's preconditioner solve.
+constexpr int kNumTables = 6;
+constexpr int kPcgTable = 5;
 // Classical scheme: default PCG tolerance (relative residual) and iterations.
 constexpr double kPcgTol = 1e-12;
 constexpr int kPcgMaxIter = 40;
@@ -59,7 +59,7 @@ int log2_exact(int n) {
 
 int table_of_level(int64_t n) { return n == 0 ? 0 : (n == 1 ? 1 : 2 + (int)(n % 3)); }
 
-// A level whose step uses table t (t < kSolveTable).
+// A level whose step uses table t (t < kPcgTable).
 int64_t level_of_table(int t) {
   if (t <= 1) return t;
   const int r = t - 2;
@@ -97,12 +97,17 @@ template <typename TM> struct Launch {
     hipLaunchKernelGGL((k_row_idct<TM, N, V>), dim3(grid), dim3(row_idct_threads<TM>(N, V)), 0, st,
                        b.m, b.idx, b.per);
   }
-  using RD = void (*)(hipStream_t, int, const double*, TM*, int, int, const int*);
-  template <int N>
-  static void rd(hipStream_t st, int grid, const double* src, TM* mid, int slot, int ny,
-                 const int* skip) {
-    hipLaunchKernelGGL((k_row_dct_field<TM, N>), dim3(grid), dim3(line_threads(N)), 0, st, src,
-                       mid, slot, ny, skip);
+  using S = void (*)(hipStream_t, const SolveArgs&);
+  template <int N> static void solve_rows(hipStream_t st, const SolveArgs& a) {
+    hipLaunchKernelGGL((k_solve_rows<TM, N>), dim3(a.ny / 2), dim3(line_threads(N)), 0, st, a);
+  }
+  template <int N> static void solve_cols(hipStream_t st, const SolveArgs& a) {
+    hipLaunchKernelGGL((k_solve_cols<TM, N>), dim3(a.nx / 2, solve_split(a.nx, a.ny) ? 2 : 1),
+                       dim3(line_threads(N)), 0, st, a);
+  }
+  template <int N, int V> static void solve_inv(hipStream_t st, const SolveArgs& a) {
+    hipLaunchKernelGGL((k_solve_inv<TM, N, V>), dim3(a.ny / row_idct_rows<TM>(N, V)),
+                       dim3(row_idct_threads<TM>(N, V)), 0, st, a);
   }
 
   template <int... L> struct Tables {
@@ -113,7 +118,10 @@ template <typename TM> struct Launch {
         {&col_solve<(1 << L), 0>...}, {&col_solve<(1 << L), 1>...}};
     static constexpr K t_row_idct[kNumVariants][sizeof...(L)] = {
         {&row_idct<(1 << L), 0>...}, {&row_idct<(1 << L), 1>...}};
-    static constexpr RD t_rd[] = {&rd<(1 << L)>...};
+    static constexpr S t_solve_rows[] = {&solve_rows<(1 << L)>...};
+    static constexpr S t_solve_cols[] = {&solve_cols<(1 << L)>...};
+    static constexpr S t_solve_inv[kNumVariants][sizeof...(L)] = {
+        {&solve_inv<(1 << L), 0>...}, {&solve_inv<(1 << L), 1>...}};
   };
   using T = Tables<4, 5, 6, 7, 8, 9, 10, 11, 12, 13>;
 };
@@ -419,7 +427,7 @@ struct Member {
   double* lamx;
   double* lamy;
   double* colsum;
-  double* unit_coef;       // {1, 0, 0, 0, 0, 1, 0, 0} for the standalone solve
+  double* unit_coef;       // {1, 0, 0, 0, 0, 1, 0, 0} for the preconditioner solve
   DevScalars* ds;
   StencilShape sh;
   // GEMM variant: per direction, the orthonormal DCT-II matrix D and its
@@ -492,6 +500,12 @@ struct ccmsav_ctx {
 
 namespace {
 
+// The BDF2 operators of member parameters p (App. B Step 3).
+OpConst solve_operators(const ccmsav_params& p) {
+  const StepConst k = make_const(p, true);
+  return {k.C1, k.C2, k.C3, k.alpha, k.lam};
+}
+
 MemberArgs member_args(const Member& m, int precision, int table) {
   MemberArgs a{};
   const bool inc = is_inc(precision);
@@ -525,16 +539,6 @@ MemberArgs member_args(const Member& m, int precision, int table) {
     a.phi_new = to_global(m.cl_z);
     a.psi_new = to_global(m.cl_z ? m.cl_z + (size_t)m.p.nx * m.p.ny : nullptr);
     a.skip = to_global<const int>(m.cl_sc ? &m.cl_sc->done_all : nullptr);
-    return a;
-  }
-  if (table == kSolveTable) {
-    // chi^{-1} and zeta^{-1} of the single field in slot M_F (App. C).
-    a.k = make_const(m.p, true);
-    a.coef = to_global<const double>(m.unit_coef);
-    a.chi_base = M_F;
-    a.nchi = 1;
-    a.zeta_base = M_F;
-    a.nzeta = 1;
     return a;
   }
   const int64_t lv = level_of_table(table);
@@ -1364,7 +1368,7 @@ size_t per_col_buffer(int nx, int ny) { return (size_t)(nx / 2 + 1) * per_col_st
 // read rhs before the inverse rows write).
 int periodic_solve(ccmsav_ctx* c, const double* rhs, double* out_chi, double* out_zeta) {
   const Member& m = c->mem[0];
-  const StepConst& k = c->h_args[(size_t)kSolveTable * c->mem.size()].k;
+  const OpConst k = solve_operators(m.p);
   const PerConst pc{k.C1, k.C2, k.C3, k.alpha, k.lam, m.p.h};
   const int nx = m.p.nx, ny = m.p.ny;
   if (m.lx > kPerMaxLog || m.ly > kPerMaxLog) return CCMSAV_EUNSUPPORTED;
@@ -1421,44 +1425,48 @@ void periodic_step_solves(const Member& m, hipStream_t st, const PerConst& pc) {
   PT::t_inv[m.lx - kMinLog](st, ny / 2, PER_FIELDS, inv, ny, cs);
 }
 
-// Upload `a` (a copy of the standalone-solve table entry, with the operator
-// constants to use) as that entry, with the outputs of member 0's solve: an
-// output that is not requested goes to intermediate slots 2-3, which the
-// solve does not read.
-int set_solve_args(ccmsav_ctx* c, MemberArgs a, double* out_chi, double* out_zeta) {
+// chi^{-1} rhs and zeta^{-1} rhs by the kernels of solve_kernels.hpp on stream
+// st (row inverse variant vi).
+void launch_solve(const SolveArgs& a, int precision, int lx, int ly, int vi, hipStream_t st) {
+  auto run = [&](auto tm) {
+    using LT = typename Launch<decltype(tm)>::T;
+    LT::t_solve_rows[lx - kMinLog](st, a);
+    LT::t_solve_cols[ly - kMinLog](st, a);
+    LT::t_solve_inv[vi][lx - kMinLog](st, a);
+  };
+  if (precision != CCMSAV_FP64)
+    run(0.0f);
+  else
+    run(0.0);
+}
+
+// The arguments of member 0's standalone solve with Neumann boundaries and
+// the operators k: an output that is not requested goes to intermediate slots
+// 2-3, which the solve does not read.
+SolveArgs solve_args(ccmsav_ctx* c, const OpConst& k, const double* rhs, double* out_chi,
+                     double* out_zeta) {
   const Member& m = c->mem[0];
   const size_t me = mid_elem(c->precision);
   double* tmp = reinterpret_cast<double*>(static_cast<char*>(m.mid) +
                                           2 * strip_field(m.p.nx, m.p.ny, (int)me) * me);
-  a.phi_new = to_global(out_chi ? out_chi : tmp);
-  a.psi_new = to_global(out_zeta ? out_zeta : tmp);
-  MemberArgs* d = c->d_args + (size_t)kSolveTable * c->mem.size();
-  HIP_TRY(hipMemcpyAsync(d, &a, sizeof(MemberArgs), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  return CCMSAV_OK;
+  SolveArgs a{};
+  a.rhs = to_global(rhs);
+  a.mid = to_global(m.mid);
+  a.outc = to_global(m.outc);
+  a.lamx = to_global(m.lamx);
+  a.lamy = to_global(m.lamy);
+  a.out_chi = to_global(out_chi ? out_chi : tmp);
+  a.out_zeta = to_global(out_zeta ? out_zeta : tmp);
+  a.nx = m.p.nx;
+  a.ny = m.p.ny;
+  a.h = m.p.h;
+  a.k = k;
+  return a;
 }
 
-// chi^{-1} rhs and zeta^{-1} rhs of member 0 with the uploaded solve entry,
-// on the context's stream: row DCT-II, column solve, row DCT-III.
-void launch_solve(ccmsav_ctx* c, const double* rhs) {
+void launch_solve(ccmsav_ctx* c, const SolveArgs& a) {
   const Member& m = c->mem[0];
-  const MemberArgs* d = c->d_args + (size_t)kSolveTable * c->mem.size();
-  const SizeClass& k = c->cls[0];
-  auto run = [&](auto tm) {
-    using TM = decltype(tm);
-    using LT = typename Launch<TM>::T;
-    LT::t_rd[m.lx - kMinLog](c->stream, m.p.ny, rhs, static_cast<TM*>(m.mid), M_F, m.p.ny,
-                             nullptr);
-    LT::t_col_solve[k.var[TUNE_COL_SOLVE]][m.ly - kMinLog](c->stream, m.p.nx,
-                                                           Batch{d, k.d_idx, m.p.nx});
-    const int vi = k.var[TUNE_ROW_IDCT];
-    const int per = m.p.ny / row_idct_rows<TM>(m.p.nx, vi);
-    LT::t_row_idct[vi][m.lx - kMinLog](c->stream, per, Batch{d, k.d_idx, per});
-  };
-  if (c->precision != CCMSAV_FP64)
-    run(0.0f);
-  else
-    run(0.0);
+  launch_solve(a, c->precision, m.lx, m.ly, c->cls[0].var[TUNE_ROW_IDCT], c->stream);
 }
 
 // ---- allocation-free standalone solve ------------------------------------------
@@ -1469,37 +1477,11 @@ constexpr int kNoallocMaxN = 1 << kNoallocMaxLog;
 // Scratch of one call, sized for FP64 intermediates at the largest grid:
 // the row-transformed right-hand side (one strip-major field, which also
 // takes an output that is not requested once the column solve has read it),
-// the two column-solved fields, the two eigenvalue tables, the unit
-// combination weights, the argument block and the member index.
+// the two column-solved fields and the two eigenvalue tables.
 constexpr size_t kNoallocField = strip_field(kNoallocMaxN, kNoallocMaxN, 8) * 8;
 constexpr size_t kNoallocLayout =
-    align_up_c(kNoallocField) + align_up_c(2 * kNoallocField) + 2 * align_up_c(kNoallocMaxN * 8) +
-    align_up_c(8 * sizeof(double)) + align_up_c(sizeof(MemberArgs)) + align_up_c(sizeof(int));
+    align_up_c(kNoallocField) + align_up_c(2 * kNoallocField) + 2 * align_up_c(kNoallocMaxN * 8);
 static_assert(kNoallocLayout <= CCMSAV_NOALLOC_SCRATCH_BYTES, "scratch layout exceeds its size");
-static_assert(sizeof(MemberArgs) % sizeof(uint64_t) == 0, "argument block copied as 8-byte words");
-
-// Operator tables, unit weights, argument block and member index of one
-// allocation-free solve, written on the device (no host-to-device copy).
-__global__ void __launch_bounds__(256)
-k_noalloc_setup(MemberArgs a, gptr<MemberArgs> args, gptr<int> idx, gptr<double> lamx,
-                gptr<double> lamy, gptr<double> coef, int nx, int ny, double h) {
-  const int tid = threadIdx.x;
-  // Eigenvalues of -Delta_h per direction (App. C): (4/h^2) sin^2(pi k / (2 n)).
-  for (int k = tid; k < nx; k += blockDim.x) {
-    const double s = sin(M_PI * k / (2.0 * nx));
-    lamx[k] = 4.0 / (h * h) * s * s;
-  }
-  for (int k = tid; k < ny; k += blockDim.x) {
-    const double s = sin(M_PI * k / (2.0 * ny));
-    lamy[k] = 4.0 / (h * h) * s * s;
-  }
-  if (tid < 8) coef[tid] = (tid == 0 || tid == 5) ? 1.0 : 0.0;
-  const uint64_t* src = reinterpret_cast<const uint64_t*>(&a);
-  const auto dst = reinterpret_cast<gptr<uint64_t>>(args);
-  for (int i = tid; i < (int)(sizeof(MemberArgs) / sizeof(uint64_t)); i += blockDim.x)
-    dst[i] = src[i];
-  if (tid == 0) idx[0] = 0;
-}
 
 // Device address of the scratch array on each device, looked up once per
 // device with that device current.
@@ -1982,10 +1964,7 @@ int32_t ccmsav_tuning(const ccmsav_ctx* c, int32_t max_shapes, int32_t* info, do
 
 int ccmsav_elliptic_solve(ccmsav_ctx* c, const double* rhs, double* out_chi, double* out_zeta) {
   if (!c || !rhs || c->mem.size() != 1) return CCMSAV_EINVAL;
-  const int r = set_solve_args(c, c->h_args[(size_t)kSolveTable * c->mem.size()], out_chi,
-                               out_zeta);
-  if (r != CCMSAV_OK) return r;
-  launch_solve(c, rhs);
+  launch_solve(c, solve_args(c, solve_operators(c->mem[0].p), rhs, out_chi, out_zeta));
   return hipGetLastError() == hipSuccess ? CCMSAV_OK : CCMSAV_EHIP;
 }
 
@@ -1996,46 +1975,14 @@ int ccmsav_elliptic_solve_bc(ccmsav_ctx* c, int32_t bc, const double* rhs, doubl
   if (bc == CCMSAV_BC_PERIODIC) return periodic_solve(c, rhs, out_chi, out_zeta);
   if (bc != CCMSAV_BC_DIRICHLET) return CCMSAV_EINVAL;
   if (is_gemm(c->precision)) return CCMSAV_EUNSUPPORTED;
-  const Member& m = c->mem[0];
-  const int nx = m.p.nx, ny = m.p.ny;
-  const size_t cells = (size_t)nx * ny;
-  // Work space in the stencil output region (rewritten by every step): the
-  // sign-alternated right-hand side and the two eigenvalue tables.
-  double* alt = static_cast<double*>(m.rm);
-  double* lx_d = alt + cells;
-  double* ly_d = lx_d + nx;
-  // Dirichlet eigenvalues of -Delta_h, (4/h^2) sin^2(pi (k+1) / (2 n)) for
-  // DST index k, at DCT index N - 1 - k: (4/h^2) cos^2(pi k' / (2 n)).
-  std::vector<double> lx(nx), ly(ny);
-  for (int k = 0; k < nx; ++k) {
-    const double cs = std::cos(M_PI * k / (2.0 * nx));
-    lx[k] = 4.0 / (m.p.h * m.p.h) * cs * cs;
-  }
-  for (int k = 0; k < ny; ++k) {
-    const double cs = std::cos(M_PI * k / (2.0 * ny));
-    ly[k] = 4.0 / (m.p.h * m.p.h) * cs * cs;
-  }
-  const bool copied =
-      hipMemcpyAsync(lx_d, lx.data(), nx * sizeof(double), hipMemcpyHostToDevice, c->stream) ==
-          hipSuccess &&
-      hipMemcpyAsync(ly_d, ly.data(), ny * sizeof(double), hipMemcpyHostToDevice, c->stream) ==
-          hipSuccess;
-  // the host tables must outlive the copies, also when one of them failed
-  if (hipStreamSynchronize(c->stream) != hipSuccess || !copied) return CCMSAV_EHIP;
-  const dim3 grid((nx + SMOOTH_THREADS - 1) / SMOOTH_THREADS, ny);
-  hipLaunchKernelGGL(k_alternate_sign, grid, dim3(SMOOTH_THREADS), 0, c->stream, rhs, alt, nx, ny);
-  MemberArgs a = c->h_args[(size_t)kSolveTable * c->mem.size()];
-  a.lamx = to_global<const double>(lx_d);
-  a.lamy = to_global<const double>(ly_d);
-  const int r = set_solve_args(c, a, out_chi, out_zeta);
-  if (r != CCMSAV_OK) return r;
-  launch_solve(c, alt);
-  if (out_chi)
-    hipLaunchKernelGGL(k_alternate_sign, grid, dim3(SMOOTH_THREADS), 0, c->stream, out_chi,
-                       out_chi, nx, ny);
-  if (out_zeta)
-    hipLaunchKernelGGL(k_alternate_sign, grid, dim3(SMOOTH_THREADS), 0, c->stream, out_zeta,
-                       out_zeta, nx, ny);
+  SolveArgs a = solve_args(c, solve_operators(c->mem[0].p), rhs, out_chi, out_zeta);
+  // the Dirichlet eigenvalues, formed by the row kernel in the stencil output
+  // region (rewritten by every step)
+  a.lamx = to_global(static_cast<double*>(c->mem[0].rm));
+  a.lamy = a.lamx + a.nx;
+  a.tables = TABLES_DIRICHLET;
+  a.alt = 1;
+  launch_solve(c, a);
   return hipGetLastError() == hipSuccess ? CCMSAV_OK : CCMSAV_EHIP;
 }
 
@@ -2053,19 +2000,14 @@ int ccmsav_smooth_ic(ccmsav_ctx* c, double M, double dt, int32_t nsteps, const d
   double* rhs = cur + cells;
   HIP_TRY(hipMemcpyAsync(cur, phi_sharp, cells * sizeof(double), hipMemcpyDefault, c->stream));
   // chi = C1 - C2 Delta_h + C3 Delta_h^2 with C1 = 1/dt, C2 = 0, C3 = M eps
-  MemberArgs a = c->h_args[(size_t)kSolveTable * c->mem.size()];
-  a.k.C1 = 1.0 / dt;
-  a.k.C2 = 0.0;
-  a.k.C3 = M * m.p.eps;
-  a.k.alpha = 1.0 / dt;      // the unused zeta output stays well defined
-  a.k.lam = 0.0;
-  const int r = set_solve_args(c, a, cur, nullptr);
-  if (r != CCMSAV_OK) return r;
+  // (the unused zeta output stays well defined)
+  const OpConst k{1.0 / dt, 0.0, M * m.p.eps, 1.0 / dt, 0.0};
+  const SolveArgs a = solve_args(c, k, rhs, cur, nullptr);
   const dim3 grid((nx + SMOOTH_THREADS - 1) / SMOOTH_THREADS, ny);
   for (int32_t s = 0; s < nsteps; ++s) {
     hipLaunchKernelGGL(k_smooth_rhs, grid, dim3(SMOOTH_THREADS), 0, c->stream, cur, rhs, nx, ny,
                        1.0 / dt, M / m.p.eps, 1.0 / (m.p.h * m.p.h));
-    launch_solve(c, rhs);
+    launch_solve(c, a);
   }
   const int blocks = (int)std::min<size_t>((cells + SMOOTH_THREADS - 1) / SMOOTH_THREADS, 4096);
   hipLaunchKernelGGL(k_clip_unit, dim3(blocks), dim3(SMOOTH_THREADS), 0, c->stream, cur, cells);
@@ -2097,41 +2039,24 @@ int ccmsav_elliptic_solve_noalloc(const ccmsav_params* p, const double* rhs, dou
     off += align_up(bytes);
     return q;
   };
-  Member m{};
-  m.p = *p;
-  m.lx = lx;
-  m.ly = ly;
-  m.sh = stencil_shape(p->nx, p->ny);
-  m.mid = take(kNoallocField);
-  m.outc = take(2 * kNoallocField);
-  m.lamx = reinterpret_cast<double*>(take(kNoallocMaxN * sizeof(double)));
-  m.lamy = reinterpret_cast<double*>(take(kNoallocMaxN * sizeof(double)));
-  m.unit_coef = reinterpret_cast<double*>(take(8 * sizeof(double)));
-  MemberArgs* d_args = reinterpret_cast<MemberArgs*>(take(sizeof(MemberArgs)));
-  int* d_idx = reinterpret_cast<int*>(take(sizeof(int)));
-  MemberArgs a = member_args(m, p->precision, kSolveTable);
+  SolveArgs a{};
+  a.rhs = to_global(rhs);
+  void* mid = take(kNoallocField);
+  a.mid = to_global(mid);
+  a.outc = to_global(static_cast<void*>(take(2 * kNoallocField)));
+  a.lamx = to_global(reinterpret_cast<double*>(take(kNoallocMaxN * sizeof(double))));
+  a.lamy = to_global(reinterpret_cast<double*>(take(kNoallocMaxN * sizeof(double))));
   // An output that is not requested goes to the row-transformed right-hand
   // side's region (FP64-sized), which the column solve has read before the
   // row inverse writes.
-  a.phi_new = to_global(out_chi ? out_chi : reinterpret_cast<double*>(m.mid));
-  a.psi_new = to_global(out_zeta ? out_zeta : reinterpret_cast<double*>(m.mid));
-  hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  hipLaunchKernelGGL(k_noalloc_setup, dim3(1), dim3(256), 0, st, a, to_global(d_args),
-                     to_global(d_idx), to_global(m.lamx), to_global(m.lamy),
-                     to_global(m.unit_coef), p->nx, p->ny, p->h);
-  const int nx = p->nx, ny = p->ny;
-  auto run = [&](auto tm) {
-    using TM = decltype(tm);
-    using LT = typename Launch<TM>::T;
-    LT::t_rd[lx - kMinLog](st, ny, rhs, static_cast<TM*>(m.mid), M_F, ny, nullptr);
-    LT::t_col_solve[0][ly - kMinLog](st, nx, Batch{d_args, d_idx, nx});
-    const int per = ny / row_idct_rows<TM>(nx, 0);
-    LT::t_row_idct[0][lx - kMinLog](st, per, Batch{d_args, d_idx, per});
-  };
-  if (p->precision != CCMSAV_FP64)
-    run(0.0f);
-  else
-    run(0.0);
+  a.out_chi = to_global(out_chi ? out_chi : static_cast<double*>(mid));
+  a.out_zeta = to_global(out_zeta ? out_zeta : static_cast<double*>(mid));
+  a.nx = p->nx;
+  a.ny = p->ny;
+  a.tables = TABLES_NEUMANN;
+  a.h = p->h;
+  a.k = solve_operators(*p);
+  launch_solve(a, p->precision, lx, ly, 0, static_cast<hipStream_t>(hip_stream));
   return hipGetLastError() == hipSuccess ? CCMSAV_OK : CCMSAV_EHIP;
 }
 

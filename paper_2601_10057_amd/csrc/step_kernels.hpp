@@ -136,17 +136,6 @@ __device__ __forceinline__ size_t mid_index(int k, int j, size_t ss) {
   return (size_t)(k >> 1) * ss + 2 * (size_t)j + (k & 1);
 }
 
-// Element (k, j) of slot f of the strip-major intermediates of an nx x ny
-// grid: one field per region (FP64), or the pair layout (FP32, mid_pair).
-template <typename TM>
-__device__ __forceinline__ size_t mid_offset(int f, int k, int j, int nx, int ny) {
-  if constexpr (sizeof(TM) == 4)
-    return mid_pair(f) * pair_field(nx, ny) + (size_t)(k >> 1) * pair_strip_stride(ny) +
-           4 * (size_t)j + 2 * (k & 1) + mid_half(f);
-  else
-    return f * strip_field(nx, ny, sizeof(TM)) + mid_index(k, j, strip_stride(ny, sizeof(TM)));
-}
-
 // Orders a wave's LDS writes before its own later reads and writes (the
 // lanes of a wave run together; this only keeps the compiler to the order).
 __device__ __forceinline__ void wave_lds_sync() {
@@ -1520,7 +1509,7 @@ __device__ __forceinline__ void col_solve_body(gptr<const TM> __restrict__ mid,
   // Combine the x-transformed right-hand sides of this group: field by field,
   // all of a field's loads in flight together (the number of fields is a
   // compile-time constant for the step's groups: 5 for chi, 2 for zeta, and
-  // 1 in a standalone solve). FP32 intermediates come in pairs: a pair whose
+  // 1 in the classical scheme's preconditioner). FP32 intermediates come in pairs: a pair whose
   // halves are consecutive slots of the group is loaded once (16 bytes a
   // row) and both halves are added in slot order, so that the sums are those
   // of the field-by-field order.
@@ -1685,7 +1674,8 @@ __device__ __forceinline__ void col_solve_body(gptr<const TM> __restrict__ mid,
 }
 
 // ---------------------------------------------------------------------------
-// P4: DCT-III along x of the two solved fields -> phi^{n+1}, psi^{n+1}.
+// P4: DCT-III along x of the two solved fields -> phi^{n+1}, psi^{n+1}. (alt:
+// the outputs of a standalone Dirichlet solve, times (-1)^(i + j).)
 // ---------------------------------------------------------------------------
 template <typename TM, int NX, int NTHR>
 __device__ __forceinline__ void row_idct_body(gptr<const TM> __restrict__ out,
@@ -1694,7 +1684,7 @@ __device__ __forceinline__ void row_idct_body(gptr<const TM> __restrict__ out,
                                               gptr<const double> __restrict__ phi_base,
                                               gptr<const double> __restrict__ psi_base,
                                               gptr<const double> __restrict__ colsum, int j,
-                                              LinesLds<TM, NX, NX>& L, int tid) {
+                                              LinesLds<TM, NX, NX>& L, int tid, int alt = 0) {
   constexpr int CPT = NX >= NTHR ? NX / NTHR : 1;            // outputs per thread
   constexpr int UPT = NX / 2 >= NTHR ? NX / 2 / NTHR : 1;    // pair units per thread
   constexpr int R = fft_radix<TM>();
@@ -1742,8 +1732,9 @@ __device__ __forceinline__ void row_idct_body(gptr<const TM> __restrict__ out,
       const int i = tid + q * NTHR;
       if (NX >= NTHR || i < NX) {
         const cpx<TM> y = line[sl.template out<q>()];
-        phi_new[(size_t)j * NX + i] = (double)y.re;
-        psi_new[(size_t)j * NX + i] = -(double)y.im;
+        const bool neg = alt & (i + j) & 1;
+        phi_new[(size_t)j * NX + i] = neg ? -(double)y.re : (double)y.re;
+        psi_new[(size_t)j * NX + i] = neg ? (double)y.im : -(double)y.im;
       }
     });
     return;
@@ -1793,7 +1784,8 @@ __device__ __forceinline__ void row_idct_band_body(gptr<const TM> __restrict__ o
                                                    gptr<const double> __restrict__ phi_base,
                                                    gptr<const double> __restrict__ psi_base,
                                                    gptr<const double> __restrict__ colsum,
-                                                   int blk, RowIdctBandLds<TM, NX>& L, int tid) {
+                                                   int blk, RowIdctBandLds<TM, NX>& L, int tid,
+                                                   int alt = 0) {
   constexpr int NTHR = row_idct_threads<TM>(NX, 0);
   constexpr int ROWS = row_idct_rows<TM>(NX, 0);
   constexpr int CPT = NX >= NTHR ? NX / NTHR : 1;            // outputs per thread and row
@@ -1857,8 +1849,9 @@ __device__ __forceinline__ void row_idct_band_body(gptr<const TM> __restrict__ o
         if (NX >= NTHR || i < NX) {
           const cpx<TM> y = line[lo[r] ^ sl.template out<q>()];
           const size_t o = (size_t)(j0 + r) * NX + i;
-          phi_new[o] = (double)y.re;
-          psi_new[o] = -(double)y.im;
+          const bool neg = alt & (i + j0 + r) & 1;
+          phi_new[o] = neg ? -(double)y.re : (double)y.re;
+          psi_new[o] = neg ? (double)y.im : -(double)y.im;
         }
       });
     }
@@ -1902,46 +1895,6 @@ __device__ __forceinline__ void row_idct_band_body(gptr<const TM> __restrict__ o
       }
     }
   }
-}
-
-// ---------------------------------------------------------------------------
-// Row DCT-II of one plain field into intermediate slot `slot` (elliptic solve).
-// ---------------------------------------------------------------------------
-template <typename TM, int NX>
-__global__ void __launch_bounds__(line_threads(NX))
-k_row_dct_field(const double* __restrict__ src, TM* __restrict__ mid, int slot, int ny,
-                const int* __restrict__ skip) {
-  if (skip && *skip) return;     // a converged iteration (whole workgroup)
-  constexpr int NTHR = line_threads(NX);
-  constexpr int CPT = NX >= NTHR ? NX / NTHR : 1;
-  constexpr int UPT = NX / 2 >= NTHR ? NX / 2 / NTHR : 1;
-  constexpr int R = fft_radix<TM>();
-  using MAP = LdsMap<TM, NX, SWZ_LINE>;
-  using LS = LineSlots<NX, NTHR, R, MAP>;
-  __shared__ cpx<TM> line[NX];
-  __shared__ cpx<double> rtab[Roots<TM, NX>::SIZE];
-  const int tid = threadIdx.x;
-  const int j = xcd_remap(blockIdx.x, gridDim.x);
-  Roots<TM, NX> rt;
-  rt.init(rtab, tid, NTHR);
-  const LS sl(tid);
-  static_for<CPT>([&](auto iq) {
-    constexpr int q = decltype(iq)::value;
-    const int i = tid + q * NTHR;
-    if (NX >= NTHR || i < NX) line[sl.template mak<q>()] = {(TM)src[(size_t)j * NX + i], (TM)0};
-  });
-  lds_sync();
-  fft_lines<TM, NX, 1, NTHR, R, MAP>(line, rt, tid);
-  static_for<UPT>([&](auto iq) {
-    constexpr int q = decltype(iq)::value;
-    const int u = tid + q * NTHR;
-    if (NX / 2 >= NTHR || u < NX / 2) {
-      TM A, B, Am, Bm;
-      dct2_unit<TM, NX>(line, sl.template bin<q>(), sl.template binm<q>(), rt, u, A, B, Am, Bm);
-      mid[mid_offset<TM>(slot, u, j, NX, ny)] = A;
-      mid[mid_offset<TM>(slot, pair_mirror<NX>(u), j, NX, ny)] = Am;
-    }
-  });
 }
 
 // ---------------------------------------------------------------------------
