@@ -494,6 +494,10 @@ struct ccmsav_ctx {
   std::vector<hipStream_t> bstream;
   std::vector<hipEvent_t> bevent;
   hipEvent_t ev_fork = nullptr;
+  // pinned host words that the field queries' error bits are written to, and
+  // the device current at creation
+  int* host_err = nullptr;
+  int device = -1;
   // resident workgroups of the stencil pass on this device ([0] FP32, [1] FP64 intermediates)
   int stencil_slots[2] = {-1, -1};
 };
@@ -1170,6 +1174,7 @@ void free_ctx(ccmsav_ctx* c) {
   for (hipEvent_t e : c->bevent) (void)hipEventDestroy(e);
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->owns_ws && c->ws) (void)hipFree(c->ws);
+  if (c->host_err) (void)hipHostFree(c->host_err);
   delete c;
 }
 
@@ -1582,6 +1587,13 @@ int ccmsav_init_batch(ccmsav_ctx** out, int32_t nmemb, const ccmsav_params* p,
     c->ws = workspace;
     c->ws_bytes = ws_bytes;
   }
+  // (without the pinned words the field queries copy instead)
+  if (hipGetDevice(&c->device) != hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&c->host_err), 2 * sizeof(int),
+                    hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    c->host_err = nullptr;
+  }
   char* base = static_cast<char*>(c->ws);
   c->d_args = reinterpret_cast<MemberArgs*>(base + BL.args);
   int* d_idx = reinterpret_cast<int*>(base + BL.idx);
@@ -1885,8 +1897,21 @@ int ccmsav_physical_energy(ccmsav_ctx* c, double out6[6]) {
 int ccmsav_get_fields_m(ccmsav_ctx* c, int32_t member, double* phi, double* psi) {
   if (!valid_member(c, member)) return CCMSAV_EINVAL;
   const Member& m = c->mem[member];
-  const size_t bytes = (size_t)m.p.nx * m.p.ny * sizeof(double);
+  const size_t cells = (size_t)m.p.nx * m.p.ny, bytes = cells * sizeof(double);
   const int s = (int)(c->level % 3);
+  // outputs in the context's device's memory leave in one kernel with the
+  // error bits
+  int dev = -1;
+  HIP_TRY(hipGetDevice(&dev));
+  if (c->host_err && dev == c->device && (!phi || on_device(phi, dev)) && (!psi || on_device(psi, dev))) {
+    const int blocks = (int)std::min<size_t>((cells / 2 + EXPORT_THREADS - 1) / EXPORT_THREADS, 4096);
+    hipLaunchKernelGGL(k_export, dim3(blocks), dim3(EXPORT_THREADS), 0, c->stream, m.phi[s],
+                       m.psi[s], phi, psi, cells, &m.ds->err,
+                       c->persistent && c->bar ? &c->bar->err : nullptr, c->host_err);
+    if (hipGetLastError() != hipSuccess) return CCMSAV_EHIP;
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return status_from_err(c->host_err[0] | (c->host_err[1] ? ERR_BARRIER : 0));
+  }
   if (phi) HIP_TRY(hipMemcpyAsync(phi, m.phi[s], bytes, hipMemcpyDefault, c->stream));
   if (psi) HIP_TRY(hipMemcpyAsync(psi, m.psi[s], bytes, hipMemcpyDefault, c->stream));
   int err = 0;

@@ -1,0 +1,53 @@
+"""Field queries to device memory (one kernel with the error bits) give the bytes that queries to
+host memory give: both fields, either one alone, members of several grids, and destinations at an
+8-byte offset; a state that is not finite is reported either way."""
+import numpy as np
+import pytest
+
+from workloads import vesicle_member
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2601_10057_amd import ccmsav as C  # noqa: E402
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_device_and_host_queries_agree(precision, offset):
+    ms = [vesicle_member(n, 70 + n, dt=2.5e-8) for n in (16, 64, 64, 256)]
+    with C.Context.ensemble([m.params for m in ms], [m.phi0 for m in ms], [m.psi0 for m in ms],
+                            precision) as ctx:
+        ctx.step(3)
+        for i, m in enumerate(ms):
+            print(f"[case] member {i} {precision} offset {offset}", flush=True)
+            ref = ctx.fields(i)
+            cells = m.phi0.size
+            buf = torch.full((2, cells + 2), -7.0, device="cuda", dtype=torch.float64)
+            phi, psi = (buf[f, offset:offset + cells].view(m.phi0.shape) for f in (0, 1))
+            ctx.fields_into(phi, None, i)
+            assert (psi == -7.0).all()
+            ctx.fields_into(None, psi, i)
+            for got, want in zip((phi, psi), ref):
+                assert np.array_equal(got.cpu().numpy(), want)
+            buf[:, offset:offset + cells] = 0.0
+            ctx.fields_into(phi, psi, i)
+            for got, want in zip((phi, psi), ref):
+                assert np.array_equal(got.cpu().numpy(), want)
+            rest = torch.cat([buf[:, :offset], buf[:, offset + cells:]], 1)
+            assert (rest == -7.0).all()
+
+
+def test_a_device_query_reports_a_state_that_is_not_finite():
+    m = vesicle_member(64, 5)
+    with C.Context(dict(m.params, dt=1e300), m.phi0, m.psi0) as ctx:
+        ctx.step(3)
+        phi = torch.empty(64, 64, device="cuda", dtype=torch.float64)
+        with pytest.raises(C.CcmsavError) as host:
+            ctx.fields()
+        with pytest.raises(C.CcmsavError) as dev:
+            ctx.fields_into(phi, phi.clone())
+        assert dev.value.code == host.value.code
