@@ -51,6 +51,19 @@ __device__ __forceinline__ int opaque_vgpr(int x) {
   return x;
 }
 
+// x, loaded from a scalar address, in a pair of scalar registers from here on
+// (the compiler may not load it again).
+__device__ __forceinline__ double held(double x) {
+  __asm__ volatile("" : "+s"(x));
+  return x;
+}
+
+// x in a vector register from here on.
+__device__ __forceinline__ double held_vgpr(double x) {
+  __asm__ volatile("" : "+v"(x));
+  return x;
+}
+
 // Computes x here: what it is formed from need not be held any longer.
 __device__ __forceinline__ void pin_vgpr(double& x) { __asm__ volatile("" : "+v"(x)); }
 
@@ -245,23 +258,17 @@ static_assert(mid_pair(RowPairs<float>::A[0]) == mid_pair(RowPairs<float>::B[0])
                   mid_half(RowPairs<float>::B[3]) == 1,
               "the FP32 row pass's FFT pairs are the layout pairs");
 
-__device__ __forceinline__ double ptilde(const StepConst& c, double psi, double p) {
-  return 0.5 * (c.gamma_in * (1.0 + p) * (psi - c.psi_in) +
-                c.gamma_out * (1.0 - p) * (psi - c.psi_out));
-}
-
 // Value of lane i - 1 (lane_from_below) or lane i + 1 (lane_from_above) of the
 // wave, by DPP whole-wave shifts of both halves of the double; the end lanes
-// get their own value back.
+// get zero (bound_ctrl: with an old value to keep, every shift needs a move
+// into its destination first). All lanes of the wave have to be active.
 __device__ __forceinline__ double lane_from_below(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x138, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xf, 0xf, false));
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xf, 0xf, true));
 }
 __device__ __forceinline__ double lane_from_above(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x130, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xf, 0xf, false));
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xf, 0xf, true));
 }
 
 // P1a: the stencil terms of a unit: SW_OUT consecutive output columns of a
@@ -297,8 +304,8 @@ template <typename TM, int LINE, int N> struct LinesLds {
 // rows and about four more (halo rows and the first loads' latency).
 //  - Grids of more than SW_SMALL rows x segments: the band height gives a
 //    whole number of rounds of 2048 units at the least rows per wave slot.
-//    Large grids are bound by memory (N = 4096, mixed: 313 us for 80 B/cell,
-//    4.3 TB/s; bands of 32 rows on 240-column workgroups took 315), at
+//    Large grids are bound by memory (N = 4096, mixed: 306 us for 80 B/cell,
+//    4.4 TB/s; bands of 32 rows on 240-column workgroups took 315), at
 //    N = 2048 and 1024 the balance tells: 98 -> 85 us and 36 -> 30 us.
 //  - Smaller grids do not fill the device by themselves, and share it with
 //    other members in an ensemble: units of 16 rows, whose sums are formed
@@ -393,22 +400,36 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
   const size_t FS = (size_t)nx * ny;
   const double k32 = 0.75 * 1.4142135623730950488;   // 3 sqrt(2) / 4
   const double half_pi = 1.5707963267948966192;
-  const double ieps = 1.0 / c.eps;
-  // neighbour values along x (adjacent lanes, by DPP wave shifts); at the
-  // boundary the ghost is the cell itself
-  auto west = [&](double v) {
-    const double u = lane_from_below(v);
-    return at_w ? v : u;
-  };
-  auto east = [&](double v) {
-    const double u = lane_from_above(v);
-    return at_e ? v : u;
-  };
+  // The constants of the row loop, held in registers: the compiler otherwise
+  // loads them again in every row, with a wait for the scalar cache each, and
+  // forms their products there. Those read most often go to vector registers,
+  // as the scalar ones do not hold them all beside the field addresses. With
+  // the shifts and ghosts below a row takes 310 vector instructions in place
+  // of 385 (N = 2048 mixed 85 -> 79 us, ensemble of 48 x 256^2 + 16 x 512^2
+  // 175 -> 165, N = 4096 mixed 314 -> 306, FP64 400 -> 398; N = 8192, bound by
+  // memory alone, 1270 -> 1296).
+  const double ieps = held_vgpr(1.0 / c.eps), x0 = held_vgpr(c.x0), x1 = held_vgpr(c.x1);
+  const double e0 = held_vgpr(c.e0), e1 = held_vgpr(c.e1), a1 = held_vgpr(c.a1);
+  const double inv_h = held(c.inv_h), inv_h2 = held(c.inv_h2), eps = held(c.eps);
+  const double beta = held(c.beta), M0 = held(c.M0);
+  const double gamma_in = held_vgpr(c.gamma_in), gamma_out = held_vgpr(c.gamma_out);
+  const double psi_in = held_vgpr(c.psi_in), psi_out = held_vgpr(c.psi_out);
+  const double beta_in = held(c.beta_in), beta_out = held(c.beta_out);
+  const double c_lap = held_vgpr(c.M_phi * c.theta_t);
+  // (a0 and lambda, or the increment form's)
+  const double c_a = held(INC ? c.C1b : c.a0), C2 = held(INC ? c.C2 : 0.0);
+  const double C3 = held(INC ? c.C3 : 0.0), c_lam = held_vgpr(INC ? c.lam * (c.x0 - 1.0) : c.lam);
+  // Neighbour values along x (adjacent lanes, by DPP wave shifts). The ghost
+  // of a pointwise quantity is the cell itself, and the lane beyond the wall
+  // has loaded just that cell (cl), so these need no selection; the ghost of
+  // Delta_h phi^n is the cell's own value, which that lane does not hold.
+  auto west = [&](double v) { return lane_from_below(v); };
+  auto east = [&](double v) { return lane_from_above(v); };
+  // the ghost row's source; spare waves may ask for rows further out
   auto at = [&](int r) {
-    const int rr = per ? ((r % ny) + ny) % ny : min(max(r, 0), ny - 1);
-    return (size_t)rr * nx + cl;
+    const int w = !per ? r : r < 0 ? r + ny : r >= ny ? r - ny : r;
+    return (size_t)min(max(w, 0), ny - 1) * nx + cl;
   };
-
   // Pointwise quantities of one row at this column.
   struct Row {
     double phn, phm, psn, psm;    // state
@@ -428,13 +449,9 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
     w.phm = a.phm[o];
     w.psn = a.psn[o];
     w.psm = a.psm[o];
-    if (c.lag_d) {
-      w.psmm = a.psmm[o];
-      w.phmm = a.phmm[o];
-    } else {
-      w.psmm = 0.0;
-      w.phmm = 0.0;
-    }
+    // (level n - 1 again where no earlier one is kept: lag_d unset)
+    w.psmm = a.psmm[o];
+    w.phmm = a.phmm[o];
     return w;
   };
   auto make_row = [&](const Raw& v) {
@@ -443,28 +460,25 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
     w.phm = v.phm;
     w.psn = v.psn;
     w.psm = v.psm;
-    w.p = c.x0 * w.phn + c.x1 * w.phm;
-    w.q = c.x0 * w.psn + c.x1 * w.psm;
+    w.p = x0 * w.phn + x1 * w.phm;
+    w.q = x0 * w.psn + x1 * w.psm;
     sincospi(0.5 * w.p, &w.sp, &w.cp);
-    w.P = ptilde(c, w.q, w.sp);
+    w.P = 0.5 * (gamma_in * (1.0 + w.sp) * (w.q - psi_in) +
+                 gamma_out * (1.0 - w.sp) * (w.q - psi_out));
     w.dq = w.psn - w.psm;
-    if (c.lag_d) {
-      w.dl = w.psn - 2.0 * w.psm + v.psmm;
-      w.fl = 2.0 * w.phm - v.phmm;
-    } else {
-      w.dl = 0.0;
-      w.fl = 0.0;
-    }
+    w.dl = w.psn - 2.0 * w.psm + v.psmm;
+    w.fl = 2.0 * w.phm - v.phmm;
     return w;
   };
   // Delta_h phi^n of the row whose phi^n is u, with the rows above (un) and below (us).
   auto lap_n = [&](double u, double un, double us) {
-    return (east(u) + west(u) + un + us - 4.0 * u) * c.inv_h2;
+    return (east(u) + west(u) + un + us - 4.0 * u) * inv_h2;
   };
 
   double sums[P1_NSUM];
 #pragma unroll
   for (int q = 0; q < P1_NSUM; ++q) sums[q] = 0.0;
+  int neg = 0;                  // faces without positive mobility, of the whole wave
 
   // Window: rows j-1, j, j+1 (pointwise), the raw state of row j+2, and
   // Delta_h phi^n of rows j-1, j. The loop takes four rows per trip with
@@ -479,8 +493,8 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
   }
   // Mobility on the face below the current row: the previous row's north
   // face (the same operands in the same order, so the same value).
-  double m_south = mobility(0.5 * (rs.p + rc.p), c.M0);
-  auto row_step = [&](int j, const Raw& r2) {
+  double m_south = mobility(0.5 * (rs.p + rc.p), M0);
+  auto row_step = [&](int j, const Raw& r2, auto group_end) {
     double Ln = 0.0;
     if constexpr (INC) Ln = (j + 1 >= ny) ? Lc : lap_n(rn.phn, r2.phn, rc.phn);
     // neighbours along x of the current row
@@ -492,17 +506,19 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
     if constexpr (INC) {
       Le = east(Lc);
       Lw = west(Lc);
+      Le = at_e ? Lc : Le;
+      Lw = at_w ? Lc : Lw;
       dqe = east(rc.dq);
       dqw = west(rc.dq);
     }
     const double pc = rc.p, pn = rn.p, ps = rs.p;
-    const double gxe = (pe - pc) * c.inv_h, gxw = (pc - pw) * c.inv_h;
-    const double gyn = (pn - pc) * c.inv_h, gys = (pc - ps) * c.inv_h;
-    const double lap_p = (gxe - gxw + gyn - gys) * c.inv_h;
+    const double gxe = (pe - pc) * inv_h, gxw = (pc - pw) * inv_h;
+    const double gyn = (pn - pc) * inv_h, gys = (pc - ps) * inv_h;
+    const double lap_p = (gxe - gxw + gyn - gys) * inv_h;
     const double pc2 = pc * pc;
     const double cubic = pc2 * pc - pc;
-    const double eph = c.e0 * rc.phn + c.e1 * rc.phm;
-    const double eps_ = c.e0 * rc.psn + c.e1 * rc.psm;
+    const double eph = e0 * rc.phn + e1 * rc.phm;
+    const double eps_ = e0 * rc.psn + e1 * rc.psm;
     double out[M_NFIELD];
     if constexpr (INC) {
       // Increment form: the residuals f_lin - chi phi^n and g_lin - zeta psi^n,
@@ -510,36 +526,35 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
       //   a0 phi^n + a1 phi^{n-1} - alpha phi^n = -a1 (phi^n - phi^{n-1}),
       //   psi* - psi^n = (x0 - 1)(psi^n - psi^{n-1}), which carries lambda Delta;
       // Delta_h^2 phi^n is Delta_h applied to Delta_h phi^n, both with ghosts.
-      const double bih = (Le + Lw + Ln + Ls - 4.0 * Lc) * c.inv_h2;
-      out[M_F] = -c.a1 * (rc.phn - rc.phm) - c.C1b * rc.phn - c.M_phi * c.theta_t * lap_p +
-                 c.C2 * Lc - c.C3 * bih;
-      const double lap_dq = (dqe + dqw + rn.dq + rs.dq - 4.0 * rc.dq) * c.inv_h2;
-      out[M_G] = -c.a1 * rc.dq - c.lam * (c.x0 - 1.0) * lap_dq;
+      const double bih = (Le + Lw + Ln + Ls - 4.0 * Lc) * inv_h2;
+      out[M_F] = -a1 * (rc.phn - rc.phm) - c_a * rc.phn - c_lap * lap_p + C2 * Lc - C3 * bih;
+      const double lap_dq = (dqe + dqw + rn.dq + rs.dq - 4.0 * rc.dq) * inv_h2;
+      out[M_G] = -a1 * rc.dq - c_lam * lap_dq;
     } else {
-      out[M_F] = c.a0 * rc.phn + c.a1 * rc.phm - c.M_phi * c.theta_t * lap_p;
+      out[M_F] = c_a * rc.phn + a1 * rc.phm - c_lap * lap_p;
       double stab;
       if (c.classical) {
         // classical scheme (App. B remarks): lambda div(M_psi(phi*) grad psi*)
-        const double me = mobility(0.5 * (rc.p + pe), c.M0), mw = mobility(0.5 * (pw + rc.p), c.M0);
-        const double mn = mobility(0.5 * (rc.p + rn.p), c.M0);
-        const double ms = mobility(0.5 * (rs.p + rc.p), c.M0);
+        const double me = mobility(0.5 * (rc.p + pe), M0), mw = mobility(0.5 * (pw + rc.p), M0);
+        const double mn = mobility(0.5 * (rc.p + rn.p), M0);
+        const double ms = mobility(0.5 * (rs.p + rc.p), M0);
         stab = (me * (qe - rc.q) - mw * (rc.q - qw) + mn * (rn.q - rc.q) - ms * (rc.q - rs.q)) *
-               c.inv_h2;
+               inv_h2;
       } else {
-        stab = (qe + qw + rn.q + rs.q - 4.0 * rc.q) * c.inv_h2;
+        stab = (qe + qw + rn.q + rs.q - 4.0 * rc.q) * inv_h2;
       }
-      out[M_G] = c.a0 * rc.psn + c.a1 * rc.psm - c.lam * stab;
+      out[M_G] = c_a * rc.psn + a1 * rc.psm - c_lam * stab;
     }
-    const double St = pc * (pc2 - 1.0 - c.beta) * 0.5 * ieps;
-    const double Hf = k32 * (cubic * ieps - c.eps * lap_p);
+    const double St = pc * (pc2 - 1.0 - beta) * 0.5 * ieps;
+    const double Hf = k32 * (cubic * ieps - eps * lap_p);
     out[M_S] = St;
     out[M_H] = Hf;
-    const double din = rc.q - c.psi_in, dout = rc.q - c.psi_out;
-    const double fin = 0.5 * c.gamma_in * din * din + c.beta_in;
-    const double fout = 0.5 * c.gamma_out * dout * dout + c.beta_out;
+    const double din = rc.q - psi_in, dout = rc.q - psi_out;
+    const double fin = 0.5 * gamma_in * din * din + beta_in;
+    const double fout = 0.5 * gamma_out * dout * dout + beta_out;
     const double grad2 = 0.5 * (gxe * gxe + gxw * gxw + gyn * gyn + gys * gys);
     const double div_a = 0.5 * ((pc2 + pe * pe) * gxe - (pw * pw + pc2) * gxw +
-                                (pc2 + pn * pn) * gyn - (ps * ps + pc2) * gys) * c.inv_h;
+                                (pc2 + pn * pn) * gyn - (ps * ps + pc2) * gys) * inv_h;
     const double Qt = 6.0 * (pc * grad2 - div_a) + cubic * (3.0 * pc2 - 1.0) * ieps * ieps;
     const double Kt = 0.5 * half_pi * rc.cp * (fin - fout);
     out[M_Q] = Qt;
@@ -548,15 +563,20 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
     // each face's mobility once: the west face is the west lane's east face
     // (at the west wall the ghost lane's face, mobility(phi*_0), as the
     // ghost rule gives), the south face the previous row's north face
-    const double Me = mobility(0.5 * (pc + pe), c.M0), Mn = mobility(0.5 * (pc + pn), c.M0);
+    const double Me = mobility(0.5 * (pc + pe), M0), Mn = mobility(0.5 * (pc + pn), M0);
     const double Mw = lane_from_below(Me), Ms = m_south;
-    out[M_L] = (Me * (Pe - Pc) - Mw * (Pc - Pw) + Mn * (rn.P - Pc) - Ms * (Pc - rs.P)) * c.inv_h2;
+    out[M_L] = (Me * (Pe - Pc) - Mw * (Pc - Pw) + Mn * (rn.P - Pc) - Ms * (Pc - rs.P)) * inv_h2;
     out[M_P] = Pc;
+    // the east and north faces of the cell (with periodic boundaries the
+    // faces across the wrap belong to the last column and row)
+    const bool face_e = !at_e, face_n = per || j < ny - 1;
+    neg += __popcll(__ballot(out_lane && face_e && !(Me > 0.0)));
+    if (face_n) neg += __popcll(__ballot(out_lane && !(Mn > 0.0)));
     if (out_lane) {
       const size_t o = (size_t)j * nx + ci;
 #pragma unroll
       for (int f = 0; f < M_NFIELD; ++f) rm[f * FS + o] = (TM)out[f];
-      const double vq = pc2 - 1.0 - c.beta;
+      const double vq = pc2 - 1.0 - beta;
       sums[P1_RS] += vq * vq * 0.25 * ieps;
       sums[P1_ES] += St * eph;
       sums[P1_EH] += Hf * eph;
@@ -572,13 +592,8 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
         sums[P1_XK] += Kt * rc.phn;
         sums[P1_XP] += Pc * rc.psn;
       }
-      // the east and north faces of the cell (with periodic boundaries the
-      // faces across the wrap belong to the last column and row)
-      const bool face_e = per || ci < nx - 1, face_n = per || j < ny - 1;
-      if (face_e && !(Me > 0.0)) sums[P1_MOBNEG] += 1.0;
-      if (face_n && !(Mn > 0.0)) sums[P1_MOBNEG] += 1.0;
       if (c.classical) {
-        sums[P1_MBAR] += mobility(pc, c.M0);
+        sums[P1_MBAR] += mobility(pc, M0);
         mob_e[o] = face_e ? Me : 0.0;
         mob_n[o] = face_n ? Mn : 0.0;
       }
@@ -586,11 +601,11 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
         // ||d^n||^2 of the previous step over the east and north faces
         if (face_e) {
           const double g = de - rc.dl;
-          sums[P1_DLAG] += g * g * c.inv_h2 * rcp64(mobility(0.5 * (rc.fl + fe), c.M0));
+          sums[P1_DLAG] += g * g * inv_h2 * rcp64(mobility(0.5 * (rc.fl + fe), M0));
         }
         if (face_n) {
           const double g = rn.dl - rc.dl;
-          sums[P1_DLAG] += g * g * c.inv_h2 * rcp64(mobility(0.5 * (rc.fl + rn.fl), c.M0));
+          sums[P1_DLAG] += g * g * inv_h2 * rcp64(mobility(0.5 * (rc.fl + rn.fl), M0));
         }
       }
     }
@@ -598,13 +613,16 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
     m_south = Mn;
     rs = rc;
     rc = rn;
-    if (j + 1 < j1) rn = make_row(r2);
+    // (bands are whole groups of rows: only a group's last row can end one)
+    if (!decltype(group_end)::value || j + 1 < j1) rn = make_row(r2);
     Ls = Lc;
     Lc = Ln;
   };
   // acc[q][lane] += the lane's sums, which start again at zero
   auto& acc = L.acc[wave];
   auto flush = [&](bool first) {
+    sums[P1_MOBNEG] = lane == 0 ? (double)neg : 0.0;
+    neg = 0;
 #pragma unroll
     for (int q = 0; q < P1_NSUM; ++q) {
       acc[q][lane] = first ? sums[q] : acc[q][lane] + sums[q];
@@ -622,13 +640,13 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
     if (!grouped) __builtin_amdgcn_s_barrier();
     if (j >= j1) continue;
     const Raw r2 = load_raw(j + 4);
-    row_step(j, r0);
+    row_step(j, r0, std::false_type{});
     const Raw r3 = load_raw(j + 5);
-    row_step(j + 1, r1);
+    row_step(j + 1, r1, std::false_type{});
     if (j + 4 < j1) r0 = load_raw(j + 6);
-    row_step(j + 2, r2);
+    row_step(j + 2, r2, std::false_type{});
     if (j + 4 < j1) r1 = load_raw(j + 7);
-    row_step(j + 3, r3);
+    row_step(j + 3, r3, std::true_type{});
     if (grouped && j + 4 < j1) flush(j == j0);
   }
   const auto row = part + (size_t)unit * P1_NSUM;
@@ -1928,7 +1946,7 @@ __device__ __forceinline__ const MemberArgs& batch_member(const MemberArgs* __re
 // are done, each XCD working through a contiguous range of them, so that
 // neighbouring units share an L2.
 template <typename TM>
-__global__ void __launch_bounds__(STENCIL_THREADS)
+__global__ void __launch_bounds__(STENCIL_THREADS, 2)
 k_stencil(BATCH_PARAMS, int count, int total, int split) {
   __shared__ StencilLds L;
   const int g = gridDim.x, b = blockIdx.x;
