@@ -186,7 +186,8 @@ k_cl_update_rows(const double* __restrict__ b, double* __restrict__ x, double* _
   constexpr int R = fft_radix<double>();
   using MAP = LdsMap<double, NX, SWZ_LINE>;
   using LS = LineSlots<NX, NTHR, R, MAP>;
-  __shared__ cpx<double> line[NX];
+  __shared__ cpx<double> buf[NX];
+  const LdsLine<double> line(buf);
   __shared__ cpx<double> rtab[Roots<double, NX>::SIZE];
   __shared__ double red[NV * (NTHR / 64 + 1)];
   if (!INIT && sc->done_all) return;
@@ -255,7 +256,8 @@ k_cl_inv_rows(const double* __restrict__ out, const double* __restrict__ r,
   constexpr int R = fft_radix<double>();
   using MAP = LdsMap<double, NX, SWZ_LINE>;
   using LS = LineSlots<NX, NTHR, R, MAP>;
-  __shared__ cpx<double> line[NX];
+  __shared__ cpx<double> buf[NX];
+  const LdsLine<double> line(buf);
   __shared__ cpx<double> rtab[Roots<double, NX>::SIZE];
   __shared__ double red[(INIT ? 4 : 2) * (NTHR / 64 + 1)];
   if (sc->done_all) return;

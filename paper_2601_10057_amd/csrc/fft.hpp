@@ -17,7 +17,12 @@
 
 namespace ccm {
 
-template <typename T> struct cpx { T re, im; };
+// Aligned to its size: FP64 elements (the twiddle roots of every line, and the
+// FP64 lines) then move with one 16-byte LDS access. By two 8-byte ones, at a
+// stride of 16 bytes, half of the banks idled, and the LDS bound the transforms:
+// Gram pass N = 8192 mixed 1480 -> 1268 us, N = 4096 mixed 247 -> 233 and FP64
+// 478 -> 421, N = 1024 FP64 37 -> 29 and row DCT 49 -> 43.
+template <typename T> struct alignas(2 * sizeof(T)) cpx { T re, im; };
 
 // Workgroup barrier for LDS traffic only: waits for this wave's LDS operations
 // and synchronises the workgroup, while global loads and stores stay in flight
@@ -135,7 +140,9 @@ template <int N, int RADIX> struct Plan {
 // (tables in lds_swizzle.hpp) to keep the FFT stages, the Makhoul-ordered
 // loads and the digit-reversed reads free of bank conflicts. Being linear,
 // at(a ^ b) = at(a) ^ at(b): kernels form addresses as a per-thread base XOR
-// a compile-time constant.
+// a compile-time constant. The slots are byte offsets, so that an access is
+// that one XOR (scaled at each access, a shift more, the shifts were 6% of the
+// vector instructions of the Gram pass and the row DCT at N = 4096).
 template <typename T, int N, int CLS> struct LdsMap {
   using Tab = SwzTab<(int)sizeof(cpx<T>), N, CLS>;
   static constexpr int B = sizeof(cpx<T>) == 8 ? 5 : 4;
@@ -143,7 +150,16 @@ template <typename T, int N, int CLS> struct LdsMap {
     int r = x;
 #pragma unroll
     for (int b = 0; b < Tab::NC; ++b) r ^= ((x >> (B + b)) & 1) ? Tab::col[b] : 0;
-    return r;
+    return r * (int)sizeof(cpx<T>);
+  }
+};
+
+// A buffer of lines in LDS, indexed by the byte offsets of its map.
+template <typename T> struct LdsLine {
+  cpx<T>* p;
+  __device__ __forceinline__ LdsLine(cpx<T>* q) : p(q) {}
+  __device__ __forceinline__ cpx<T>& operator[](int off) const {
+    return *reinterpret_cast<cpx<T>*>(reinterpret_cast<char*>(p) + off);
   }
 };
 
@@ -192,7 +208,7 @@ __device__ __forceinline__ void apply_twiddles(const Roots<T, N>& rt, int t, cpx
 // slots are at(e0(tid)) ^ at(e0(it NTHR)) ^ at(r S). Butterflies own disjoint
 // elements; the barrier separates the stages.
 template <typename T, int N, int NL, int NTHR, int R, int L, typename MAP>
-__device__ __forceinline__ void dif_stage(cpx<T>* buf, const Roots<T, N>& rt, int tid) {
+__device__ __forceinline__ void dif_stage(LdsLine<T> buf, const Roots<T, N>& rt, int tid) {
   constexpr int NB = N / R;
   constexpr int TOT = NB * NL;
   constexpr int S = L / R;
@@ -220,7 +236,7 @@ __device__ __forceinline__ void dif_stage(cpx<T>* buf, const Roots<T, N>& rt, in
 
 template <typename T, int N, int NL, int NTHR, int L, bool FIRST, int RADIX, typename MAP>
 struct DifRunner {
-  static __device__ __forceinline__ void run(cpx<T>* buf, const Roots<T, N>& rt, int tid) {
+  static __device__ __forceinline__ void run(LdsLine<T> buf, const Roots<T, N>& rt, int tid) {
     if constexpr (L > 1) {
       constexpr int R = FIRST ? Plan<N, RADIX>::FIRST : RADIX;
       dif_stage<T, N, NL, NTHR, R, L, MAP>(buf, rt, tid);
@@ -234,7 +250,7 @@ struct DifRunner {
 // found at element digit_rev<N, RADIX>(k). The caller must have synchronised
 // after writing the input; the FFT ends with a barrier.
 template <typename T, int N, int NL, int NTHR, int RADIX, typename MAP>
-__device__ __forceinline__ void fft_lines(cpx<T>* buf, const Roots<T, N>& rt, int tid) {
+__device__ __forceinline__ void fft_lines(LdsLine<T> buf, const Roots<T, N>& rt, int tid) {
   DifRunner<T, N, NL, NTHR, N, true, RADIX, MAP>::run(buf, rt, tid);
 }
 
@@ -338,7 +354,7 @@ __device__ __forceinline__ void dct2_pair(cpx<T> z, cpx<T> zm, cpx<T> w, T s, T&
 // DCT-II post-processing of pair unit u (bins u and pair_mirror(u)) from the
 // FFT output at slots pk (bin u) and pm (its mirror).
 template <typename T, int N>
-__device__ __forceinline__ void dct2_unit(const cpx<T>* Z, int pk, int pm, const Roots<T, N>& rt,
+__device__ __forceinline__ void dct2_unit(LdsLine<T> Z, int pk, int pm, const Roots<T, N>& rt,
                                           int u, T& A, T& B, T& Am, T& Bm) {
   const cpx<T> z = Z[pk];
   const cpx<T> zm = Z[pm];

@@ -44,7 +44,8 @@ template <int NX>
 __global__ void __launch_bounds__(line_threads(NX)) k_per_rows(PerRows f, int ny, size_t cs) {
   constexpr int NTHR = line_threads(NX);
   using MAP = LdsMap<double, NX, SWZ_LINE>;
-  __shared__ cpx<double> line[NX];
+  __shared__ cpx<double> buf[NX];
+  const LdsLine<double> line(buf);
   __shared__ cpx<double> rtab[Roots<double, NX>::SIZE];
   const int tid = threadIdx.x;
   const int j = 2 * blockIdx.x;
@@ -82,8 +83,9 @@ __global__ void __launch_bounds__(line_threads(NY))
 k_per_cols(PerCols f, int nx, size_t cs, PerConst c) {
   constexpr int NTHR = line_threads(NY);
   using MAP = LdsMap<double, NY, SWZ_LINE>;
-  __shared__ cpx<double> a[NY];
-  __shared__ cpx<double> b[NY];
+  __shared__ cpx<double> abuf[NY];
+  __shared__ cpx<double> bbuf[NY];
+  const LdsLine<double> a(abuf), b(bbuf);
   __shared__ cpx<double> rtab[Roots<double, NY>::SIZE];
   const int tid = threadIdx.x;
   const int kx = blockIdx.x;
@@ -122,7 +124,8 @@ template <int NX>
 __global__ void __launch_bounds__(line_threads(NX)) k_per_rows_inv(PerInv f, int ny, size_t cs) {
   constexpr int NTHR = line_threads(NX);
   using MAP = LdsMap<double, NX, SWZ_LINE>;
-  __shared__ cpx<double> line[NX];
+  __shared__ cpx<double> buf[NX];
+  const LdsLine<double> line(buf);
   __shared__ cpx<double> rtab[Roots<double, NX>::SIZE];
   const int tid = threadIdx.x;
   const int j = 2 * blockIdx.x;

@@ -48,6 +48,7 @@ __global__ void __launch_bounds__(line_threads(NX)) k_solve_rows(SolveArgs a) {
   using MAP = LdsMap<TM, NX, SWZ_LINE>;
   using LS = LineSlots<NX, NTHR, R, MAP>;
   __shared__ LinesLds<TM, NX, NX> L;
+  const LdsLine<TM> line(L.line);
   const int tid = threadIdx.x;
   const int j = 2 * xcd_remap(blockIdx.x, gridDim.x);
   if (a.tables != TABLES_GIVEN) {
@@ -70,14 +71,14 @@ __global__ void __launch_bounds__(line_threads(NX)) k_solve_rows(SolveArgs a) {
       // j is even: row j has the sign of column i, row j + 1 the other one
       const double u = src[i], w = src[NX + i];
       const bool neg0 = a.alt & i & 1, neg1 = a.alt & ~i & 1;
-      L.line[sl.template mak<q>()] = {(TM)(neg0 ? -u : u), (TM)(neg1 ? -w : w)};
+      line[sl.template mak<q>()] = {(TM)(neg0 ? -u : u), (TM)(neg1 ? -w : w)};
     }
   });
   lds_sync();
-  fft_lines<TM, NX, 1, NTHR, R, MAP>(L.line, rt, tid);
+  fft_lines<TM, NX, 1, NTHR, R, MAP>(line, rt, tid);
   const size_t SS = strip_stride(a.ny, sizeof(TM));
   const auto mid = static_cast<gptr<TM>>(a.mid);
-  row_dct_pairs<TM, NX, NTHR, MAP>(L.line, rt, tid, [&](int sp, TM a0, TM a1, TM b0, TM b1) {
+  row_dct_pairs<TM, NX, NTHR, MAP>(line, rt, tid, [&](int sp, TM a0, TM a1, TM b0, TM b1) {
     RowPiece<TM, 2> pc;
     pc.v[0] = a0;
     pc.v[1] = a1;
@@ -107,7 +108,7 @@ __global__ void __launch_bounds__(line_threads(NY)) k_solve_cols(SolveArgs a) {
   const int tid = threadIdx.x;
   const int s = xcd_remap(blockIdx.x, gridDim.x);
   const size_t SS = strip_stride(NY, sizeof(TM)), FSM = strip_field(a.nx, NY, sizeof(TM));
-  cpx<TM>* line = L.line;
+  const LdsLine<TM> line(L.line);
   Roots<TM, NY> rt;
   rt.init(L.rtab, tid, NTHR);
   const LS sl(tid);

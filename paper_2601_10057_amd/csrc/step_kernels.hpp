@@ -404,8 +404,8 @@ __device__ __forceinline__ void stencil_body(const RowArgs& a, gptr<TM> __restri
   // loads them again in every row, with a wait for the scalar cache each, and
   // forms their products there. Those read most often go to vector registers,
   // as the scalar ones do not hold them all beside the field addresses. With
-  // the shifts and ghosts below a row takes 310 vector instructions in place
-  // of 385 (N = 2048 mixed 85 -> 79 us, ensemble of 48 x 256^2 + 16 x 512^2
+  // the shifts and ghosts below a row takes 340 vector instructions in place
+  // of 405 (N = 2048 mixed 85 -> 79 us, ensemble of 48 x 256^2 + 16 x 512^2
   // 175 -> 165, N = 4096 mixed 314 -> 306, FP64 400 -> 398; N = 8192, bound by
   // memory alone, 1270 -> 1296).
   const double ieps = held_vgpr(1.0 / c.eps), x0 = held_vgpr(c.x0), x1 = held_vgpr(c.x1);
@@ -738,7 +738,7 @@ __device__ __forceinline__ void row_dct8_body(gptr<const TM> __restrict__ rm,
   constexpr int NTHR = line_threads(NX);
   constexpr int ROWS = p1_rows_v<TM>(NX, V);
   constexpr int NP = p1_pairs_v<TM>(NX, V);
-  cpx<TM>* line = L.line;
+  const LdsLine<TM> line(L.line);
   cpx<double>* rtab = L.rtab;
   const int j0 = blk * ROWS;
   const size_t FS = (size_t)NX * ny;                            // row-major fields
@@ -873,7 +873,7 @@ __device__ __forceinline__ void row_dct8_body(gptr<const TM> __restrict__ rm,
 // complex line) by column pairs: store(sp, A_2sp, A_2sp+1, B_2sp, B_2sp+1).
 // The slots of bins 2 sp, 2 sp + 1 and their mirrors as in row_dct8_body.
 template <typename TM, int NX, int NTHR, typename MAP, typename F>
-__device__ __forceinline__ void row_dct_pairs(const cpx<TM>* line, const Roots<TM, NX>& rt,
+__device__ __forceinline__ void row_dct_pairs(LdsLine<TM> line, const Roots<TM, NX>& rt,
                                               int tid, F&& store) {
   using LS = LineSlots<NX, NTHR, fft_radix<TM>(), MAP>;
   constexpr int SPT = NX / 2 >= NTHR ? NX / 2 / NTHR : 1;
@@ -948,7 +948,7 @@ __device__ __forceinline__ void fetch_strip_first(gptr<const cpx<TM>> __restrict
 // reads of this one need no barrier behind them.
 template <typename TM, int NY, int LPT, int UPT, int NTHR, int R, typename MAP,
           bool FIRST_IN_REGS = false, bool TRAIL_SYNC = true>
-__device__ __forceinline__ void column_dct2(const StripRegs<TM, LPT>& in, cpx<TM>* line,
+__device__ __forceinline__ void column_dct2(const StripRegs<TM, LPT>& in, LdsLine<TM> line,
                                             const Roots<TM, NY>& rt,
                                             const LineSlots<NY, NTHR, R, MAP>& sl, int tid,
                                             TM (&A)[2 * UPT], TM (&B)[2 * UPT]) {
@@ -996,6 +996,9 @@ template <typename TM, int NY> struct GramPlan {
   static constexpr bool F32 = sizeof(TM) == 4;
   static constexpr int NTHR = gram_threads<TM>(NY);
   static constexpr int WAVES = NTHR / 64;
+  // one butterfly per thread in each FFT stage
+  static constexpr int RADIX =
+      NY / NTHR >= 16 ? 16 : NY / NTHR >= 8 ? 8 : NY / NTHR >= 4 ? 4 : 2;
   static constexpr int ELEM = (int)sizeof(cpx<TM>);
   static constexpr bool DBL = F32 && NTHR == 512;
   static constexpr int LINE = (DBL ? 2 : 1) * NY;
@@ -1046,8 +1049,7 @@ __device__ __forceinline__ void col_gram_body(gptr<const TM> __restrict__ mid,
   constexpr int LPT = NY >= NTHR ? NY / NTHR : 1;            // loads per thread
   constexpr int UPT = NY / 2 >= NTHR ? NY / 2 / NTHR : 1;    // pair units per thread
   constexpr int KPT = 2 * UPT;                               // bins per thread
-  // Radix with one butterfly per thread in each FFT stage.
-  constexpr int GR = NY / NTHR >= 16 ? 16 : NY / NTHR >= 8 ? 8 : NY / NTHR >= 4 ? 4 : 2;
+  constexpr int GR = GP::RADIX;
   using MAP = LdsMap<TM, NY, SWZ_GRAM>;
   using LS = LineSlots<NY, NTHR, GR, MAP>;
   Roots<TM, NY> rt;
@@ -1532,7 +1534,7 @@ __device__ __forceinline__ void col_solve_body(gptr<const TM> __restrict__ mid,
   constexpr int R = fft_radix<TM>();
   using MAP = LdsMap<TM, NY, SWZ_LINE>;
   using LS = LineSlots<NY, NTHR, R, MAP>;
-  cpx<TM>* line = L.line;
+  const LdsLine<TM> line(L.line);
   cpx<double>* rtab = L.rtab;
   const int nstrip = nx / 2;
   const int s = lin % nstrip;
@@ -1697,7 +1699,7 @@ __device__ __forceinline__ void col_solve_body(gptr<const TM> __restrict__ mid,
     // rounding noise instead of zero. Hand the row-inverse pass FP64 targets
     // for the row sums that add up to zero, so that the increment it writes
     // has zero sum in FP64 arithmetic. (Other strips pass the barriers only.)
-    double* buf = reinterpret_cast<double*>(line);   // the line is no longer read
+    double* buf = reinterpret_cast<double*>(line.p);   // the line is no longer read
     lds_sync();
 #pragma unroll
     for (int q = 0; q < LPT; ++q) {
@@ -1730,7 +1732,7 @@ __device__ __forceinline__ void row_idct_body(gptr<const TM> __restrict__ out,
   constexpr int R = fft_radix<TM>();
   using MAP = LdsMap<TM, NX, SWZ_LINE>;
   using LS = LineSlots<NX, NTHR, R, MAP>;
-  cpx<TM>* line = L.line;
+  const LdsLine<TM> line(L.line);
   cpx<double>* rtab = L.rtab;
   const size_t SS = strip_stride(ny, sizeof(TM));
   const size_t FSM = strip_field(NX, ny, sizeof(TM));
@@ -1789,7 +1791,7 @@ __device__ __forceinline__ void row_idct_body(gptr<const TM> __restrict__ out,
     Y[q] = {(TM)0, (TM)0};
     if (NX >= NTHR || i < NX) Y[q] = line[sl.template out<q>()];
   });
-  double* buf = reinterpret_cast<double*>(line);     // the line is no longer read
+  double* buf = reinterpret_cast<double*>(line.p);     // the line is no longer read
   lds_sync();
 #pragma unroll
   for (int q = 0; q < CPT; ++q) {
@@ -1834,7 +1836,7 @@ __device__ __forceinline__ void row_idct_band_body(gptr<const TM> __restrict__ o
   constexpr int RS = NX * (int)sizeof(cpx<TM>) / (int)sizeof(double);   // row buffer stride
   using MAP = LdsMap<TM, NX, SWZ_ROW>;
   using LS = LineSlots<NX, NTHR, R, MAP>;
-  cpx<TM>* line = L.line;
+  const LdsLine<TM> line(L.line);
   cpx<double>* rtab = L.rtab;
   const int j0 = blk * ROWS;
   const size_t SS = strip_stride(ny, sizeof(TM));
@@ -1909,7 +1911,7 @@ __device__ __forceinline__ void row_idct_band_body(gptr<const TM> __restrict__ o
       if (NX >= NTHR || i < NX) Y[r][q] = line[lo[r] ^ sl.template out<q>()];
     });
   }
-  double* buf = reinterpret_cast<double*>(line);     // the lines are no longer read
+  double* buf = reinterpret_cast<double*>(line.p);     // the lines are no longer read
   lds_sync();
 #pragma unroll
   for (int r = 0; r < ROWS; ++r) {
