@@ -1078,6 +1078,15 @@ int enqueue_step_level(ccmsav_ctx* c, int64_t level, hipStream_t st,
           c->cls[ki].tune_ms[tk][v] = mn;
           if (mn < c->cls[ki].tune_ms[tk][best]) best = v;
         }
+        // On its own, on rows long since in memory, the FP32 row DCT of long
+        // lines takes about the same time in both bands; behind the stencil the half one
+        // is faster (N = 4096: 293 and 295 us alone, 285 and 274 in a step;
+        // N = 2048: 78 and 78, 77 and 65), so near ties go to it (N = 8192:
+        // 1410 and 1580 us alone, 1390 and 1560).
+        const float* ms = c->cls[ki].tune_ms[tk];
+        if (tk == TUNE_ROW_DCT && c->precision == CCMSAV_MIXED && c->cls[ki].lx >= 11 &&
+            ms[1] < 1.05f * ms[0])
+          best = 1;
         c->cls[ki].var[tk] = best;
       }
     for (hipEvent_t e : tu.ev)

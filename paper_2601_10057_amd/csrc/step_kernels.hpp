@@ -763,11 +763,14 @@ __device__ __forceinline__ void row_dct8_body(gptr<const TM> __restrict__ rm,
   constexpr int SPT = NX / 2 >= SPL ? NX / 2 / SPL : 1;      // passes
   const TM S0 = (TM)(0.5 * sqrt(1.0 / NX)), S1 = (TM)(0.5 * sqrt(2.0 / NX));
 
-  // The next round's rows are loaded while the current one is transformed:
-  // behind the stores of a round they would have to wait for those as well
-  // (N = 4096: 301 -> 279 us, FP64 677 -> 660).
+  // FP32: the next round's rows are loaded while the current one is
+  // transformed; behind the stores of a round they would have to wait for
+  // those as well (N = 4096: 298 -> 279 us). Not by the band of 8192 points,
+  // which has no registers left for them, nor in FP64, where the stores bound
+  // the kernel and loads in between spread them (N = 4096: 643 us, with loads
+  // ahead 705).
   constexpr int ROUNDS = 4 / NP;
-  constexpr bool AHEAD = !(sizeof(TM) == 4 && NX >= 8192 && V == 0);
+  constexpr bool AHEAD = sizeof(TM) == 4 && !(NX >= 8192 && V == 0);
   cpx<TM> next[ROWS * NP][CPT];
   auto fetch = [&](auto ir, int t) {
     constexpr int r = decltype(ir)::value;
