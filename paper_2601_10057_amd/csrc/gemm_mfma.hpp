@@ -28,7 +28,6 @@ namespace ccm {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
 
 enum MfMode { MF_ROW = 0, MF_COL = 1 };
 
@@ -53,18 +52,26 @@ __device__ __forceinline__ int mf_slot(int line, int k8) {
 constexpr int MF_PARTS = 3;
 
 // x = x_0 + x_1 + x_2 + O(2^-25 |x|): three bfloat16 parts of eight FP32
-// values, each the rounding of what the earlier parts leave.
+// values, each the rounding (to nearest even) of what the earlier parts leave.
+// The conversion instruction takes two values at a time: 44 vector instructions
+// per eight values, where rounding by integer arithmetic took twice as many
+// (N = 8192: forward products along y 287 -> 275 and 1838 -> 1732 us).
 __device__ __forceinline__ void split8(const float (&v)[8], bf16x8_t (&part)[MF_PARTS]) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   float r[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = v[e];
 #pragma unroll
   for (int q = 0; q < MF_PARTS; ++q) {
-    u16x8_t h;
+    u32x4 h;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      h[e] = bf16_rne(r[e]);
-      r[e] -= bf16_to_f32(h[e]);
+    for (int p = 0; p < 4; ++p) {
+      const f32x2 x = {r[2 * p], r[2 * p + 1]};
+      h[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+      r[2 * p] -= __uint_as_float(h[p] << 16);
+      r[2 * p + 1] -= __uint_as_float(h[p] & 0xffff0000u);
     }
     part[q] = __builtin_bit_cast(bf16x8_t, h);
   }
