@@ -1174,6 +1174,37 @@ int read_err(ccmsav_ctx* c, int* err) {
   return CCMSAV_OK;
 }
 
+// Pairs of pinned words for the contexts' field queries, 256 of them in one 4 KB
+// allocation of the process: an allocation and a release of its own took 20 us
+// each, a sixth of what the creation of a small context takes. Contexts beyond
+// them do without (their queries copy).
+constexpr int kPinnedPairs = 256, kPinnedInts = 4;
+std::mutex g_pinned_mu;
+int* g_pinned = nullptr;
+bool g_pinned_used[kPinnedPairs];
+
+int* take_pinned() {
+  std::lock_guard<std::mutex> lock(g_pinned_mu);
+  if (!g_pinned && hipHostMalloc(reinterpret_cast<void**>(&g_pinned),
+                                 kPinnedPairs * kPinnedInts * sizeof(int),
+                                 hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    g_pinned = nullptr;
+    return nullptr;
+  }
+  for (int i = 0; i < kPinnedPairs; ++i)
+    if (!g_pinned_used[i]) {
+      g_pinned_used[i] = true;
+      return g_pinned + i * kPinnedInts;
+    }
+  return nullptr;
+}
+
+void give_pinned(int* words) {
+  std::lock_guard<std::mutex> lock(g_pinned_mu);
+  g_pinned_used[(words - g_pinned) / kPinnedInts] = false;
+}
+
 void free_ctx(ccmsav_ctx* c) {
   if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
   if (c->ev_in) (void)hipEventDestroy(c->ev_in);
@@ -1183,7 +1214,7 @@ void free_ctx(ccmsav_ctx* c) {
   for (hipEvent_t e : c->bevent) (void)hipEventDestroy(e);
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->owns_ws && c->ws) (void)hipFree(c->ws);
-  if (c->host_err) (void)hipHostFree(c->host_err);
+  if (c->host_err) give_pinned(c->host_err);
   delete c;
 }
 
@@ -1597,12 +1628,10 @@ int ccmsav_init_batch(ccmsav_ctx** out, int32_t nmemb, const ccmsav_params* p,
     c->ws_bytes = ws_bytes;
   }
   // (without the pinned words the field queries copy instead)
-  if (hipGetDevice(&c->device) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&c->host_err), 2 * sizeof(int),
-                    hipHostMallocDefault) != hipSuccess) {
+  if (hipGetDevice(&c->device) == hipSuccess)
+    c->host_err = take_pinned();
+  else
     (void)hipGetLastError();
-    c->host_err = nullptr;
-  }
   char* base = static_cast<char*>(c->ws);
   c->d_args = reinterpret_cast<MemberArgs*>(base + BL.args);
   int* d_idx = reinterpret_cast<int*>(base + BL.idx);

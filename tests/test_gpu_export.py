@@ -51,3 +51,22 @@ def test_a_device_query_reports_a_state_that_is_not_finite():
         with pytest.raises(C.CcmsavError) as dev:
             ctx.fields_into(phi, phi.clone())
         assert dev.value.code == host.value.code
+
+
+def test_contexts_beyond_the_pinned_words_query_as_well():
+    # 256 contexts hold pinned words, further ones copy; closed ones give theirs back
+    m = vesicle_member(16, 9, dt=2.5e-8)
+    phi, psi = (torch.empty(16, 16, device="cuda", dtype=torch.float64) for _ in range(2))
+    ctxs = [C.Context(m.params, m.phi0, m.psi0) for _ in range(260)]
+    for ctx in ctxs[::2]:
+        ctx.close()
+    ctxs[::2] = [C.Context(m.params, m.phi0, m.psi0) for _ in ctxs[::2]]
+    for ctx in ctxs:
+        ctx.step(1)
+    ref = ctxs[0].fields()
+    for ctx in ctxs:
+        phi.zero_()
+        psi.zero_()
+        ctx.fields_into(phi, psi)
+        assert all(np.array_equal(a.cpu().numpy(), b) for a, b in zip((phi, psi), ref))
+        ctx.close()
