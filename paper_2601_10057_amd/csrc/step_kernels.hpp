@@ -10,8 +10,8 @@
 //   P1b k_row_dct8   : orthonormal DCT-II along x of the 8 fields for a band of
 //       rows (the band's rows of a column pair leave as one piece per FP64
 //       field or FP32 field pair).
-//   P2  k_col_gram   : per strip of two columns, DCT-II along y and the
-//       Parseval inner products (F_i, chi^{-1} F_j), (P, zeta^{-1} g), (P, zeta^{-1} L).
+//   P2  k_col_gram   : per column, DCT-II along y of its fields (two as one
+//       complex line) and the Parseval inner products (F_i, chi^{-1} F_j), (P, zeta^{-1} g), (P, zeta^{-1} L).
 //   S   k_solve      : reduces the partials, assembles and solves the 5x5
 //       system of App. B Step 4, updates the SAVs, and emits the spectral
 //       combination coefficients (all on the device).
@@ -83,13 +83,14 @@ template <typename TM> constexpr int line_threads_v(int n, int v) {
 // thread, so that four kept FP32 spectra take 32 registers and two workgroups
 // of 512 threads fit a CU at N = 4096. FP32 lines of 8192 points take sixteen
 // bins and radix-16 butterflies: one workgroup per CU either way (1024
-// threads: 1594 us, 512: 1499).
+// threads: 1594 us, 512: 1499; 1268 with 16-byte LDS accesses).
 template <typename TM> constexpr int gram_threads(int n) {
   return clamp_threads(n / (sizeof(TM) == 4 && n >= 8192 ? 16 : 8));
 }
 // Waves per SIMD the Gram kernel's registers are held to: it is bound by issue
 // and by barriers, so lines of 2048 and 4096 points take four at 128 registers
-// (N = 4096 FP64: 475 us against 590 at two; N = 2048 FP32 66 against 78).
+// (with 8-byte LDS accesses N = 4096 FP64: 475 us against 590 at two, N = 2048
+// FP32 66 against 78; 421 and 58 now).
 constexpr int gram_waves(int n) { return n == 2048 || n == 4096 ? 4 : 1; }
 // Complex lines of length n that fit in LDS next to the twiddle tables.
 template <typename TM> constexpr int lds_line_budget(int n) {
@@ -1012,7 +1013,7 @@ template <typename TM, int NY> struct GramPlan {
   static constexpr bool FRESH = !F32 || NY >= 2048;
   // The next pair's rows loaded while the current pair is transformed. The
   // shortest lines are left to the other workgroups of their CU (ensemble of
-  // 48 x 256^2 + 16 x 512^2: 101 us, with loads ahead 113).
+  // 48 x 256^2 + 16 x 512^2: 95 us, with loads ahead 103).
   static constexpr bool AHEAD = F32 && NY >= 1024;
   // FP64 lines of 8192 points: the kept spectra of eight bins do not fit the
   // 128 registers of a 1024-thread workgroup, so they go to per-thread slots
@@ -1035,9 +1036,9 @@ template <typename TM, int NY> struct GramLds {
 // fill each other's barriers, and at N = 8192 nothing spills to memory. Both
 // columns of a strip read its rows; the second read is served by the L2 (the
 // counted HBM traffic is that of one). At N = 4096 (FP32, 248 us; two columns
-// per workgroup 253 us) the VALU issues 73% of the time. Two columns side by
-// side in one workgroup of 1024 threads: 290 us; radix 16 with 256 threads:
-// 272 us.
+// per workgroup 253 us, two side by side in one of 1024 threads 290, radix 16
+// with 256 threads 272; 233 us since the roots move with 16-byte LDS accesses)
+// the VALU issues 77% of the time and the LDS is busy for 36%.
 // FRESH_SLOTS: every transform forms its LDS slots anew (the persistent
 // launch, where the kernel's register budget is shared by all passes).
 template <typename TM, int NY, bool FRESH_SLOTS = false>
