@@ -8,8 +8,11 @@
 // Both systems iterate in lock step in one set of launches; every scalar of
 // the iteration lives in device memory, so the host enqueues a fixed number
 // of iterations and the kernels of an iteration return at once when both
-// systems have converged (a flag every block reads first, uniform over the
-// block). An iteration is four kernels:
+// systems have converged. A kernel reads that from a flag that no workgroup of
+// its own launch writes, so that all waves of a workgroup take the same
+// branch: k_cl_inv_rows, which makes the stopping test and sets done_all, goes
+// by a copy of it from the start of the iteration. An iteration is four
+// kernels:
 //   k_cl_matvec       beta; p = z + beta p, q = zeta p; partial (p, q)
 //   k_cl_update_rows  a; x += a p, r -= a q; partial |r|^2; the row DCT-II of
 //                     both residuals as one complex line
@@ -47,8 +50,9 @@ struct PcgScalars {
   double pl[2];                    // (P~, x_s) with the mean correction
   int iters[2];
   int done[2];
-  int done_all;                    // read by the solve kernels (MemberArgs::skip)
-  int pad;
+  int done_all;                    // set by k_cl_inv_rows, read by the other kernels
+                                   //   (k_col_solve: MemberArgs::skip)
+  int done_before;                 // done_all as the iteration began, for k_cl_inv_rows
 };
 
 // Partial sums of the iteration's kernels, one row per workgroup.
@@ -109,7 +113,9 @@ k_cl_matvec(const double* __restrict__ z, const double* __restrict__ p_old,
             const double* __restrict__ mn, int nx, int ny, double inv_h2,
             ClPart part, PcgScalars* __restrict__ sc, int it) {
   __shared__ double red[2 * (CL_THREADS / 64 + 1)];
-  if (sc->done_all) return;
+  const int done = sc->done_all;
+  if (blockIdx.x == 0 && threadIdx.x == 0) sc->done_before = done;
+  if (done) return;
   const size_t n = (size_t)nx * ny;
   double rz[2], be[2] = {0.0, 0.0};
   cl_gather<2, CL_THREADS>(part.rz, ny, red, rz);
@@ -244,8 +250,9 @@ k_cl_update_rows(const double* __restrict__ b, double* __restrict__ x, double* _
 
 // One row of the preconditioned residuals: DCT-III along x of the two solved
 // fields as one complex line -> z, and (r, z). Workgroup 0 makes the stopping
-// test of the update before (INIT: keeps |b|^2 and sum b instead); z of an
-// iteration that has just converged is not used.
+// test of the update before (INIT: keeps |b|^2 and sum b instead); the others
+// do not wait for it, and z of an iteration that has just converged is not
+// used.
 template <int NX, bool INIT>
 __global__ void __launch_bounds__(line_threads(NX))
 k_cl_inv_rows(const double* __restrict__ out, const double* __restrict__ r,
@@ -260,7 +267,7 @@ k_cl_inv_rows(const double* __restrict__ out, const double* __restrict__ r,
   const LdsLine<double> line(buf);
   __shared__ cpx<double> rtab[Roots<double, NX>::SIZE];
   __shared__ double red[(INIT ? 4 : 2) * (NTHR / 64 + 1)];
-  if (sc->done_all) return;
+  if (!INIT && sc->done_before) return;
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {                       // whole workgroup
     if constexpr (INIT) {
