@@ -206,9 +206,14 @@ __device__ __forceinline__ void apply_twiddles(const Roots<T, N>& rt, int t, cpx
 // stores y_q exp(-2 pi i m q / L) back at x[e0 + q S]. e0 is b with log2 R
 // zero bits inserted at bit log2 S, a linear map of the bits of b, so the LDS
 // slots are at(e0(tid)) ^ at(e0(it NTHR)) ^ at(r S). Butterflies own disjoint
-// elements; the barrier separates the stages.
-template <typename T, int N, int NL, int NTHR, int R, int L, typename MAP>
-__device__ __forceinline__ void dif_stage(LdsLine<T> buf, const Roots<T, N>& rt, int tid) {
+// elements; the barrier separates the stages (`last` runs ahead of the last
+// stage's).
+struct NoHook {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <typename T, int N, int NL, int NTHR, int R, int L, typename MAP, typename F>
+__device__ __forceinline__ void dif_stage(LdsLine<T> buf, const Roots<T, N>& rt, int tid,
+                                          const F& last) {
   constexpr int NB = N / R;
   constexpr int TOT = NB * NL;
   constexpr int S = L / R;
@@ -231,16 +236,19 @@ __device__ __forceinline__ void dif_stage(LdsLine<T> buf, const Roots<T, N>& rt,
       for (int q = 0; q < R; ++q) buf[e ^ MAP::at(q * S)] = v[q];
     }
   }
+  if constexpr (L == R) last();
   lds_sync();
 }
 
 template <typename T, int N, int NL, int NTHR, int L, bool FIRST, int RADIX, typename MAP>
 struct DifRunner {
-  static __device__ __forceinline__ void run(LdsLine<T> buf, const Roots<T, N>& rt, int tid) {
+  template <typename F = NoHook>
+  static __device__ __forceinline__ void run(LdsLine<T> buf, const Roots<T, N>& rt, int tid,
+                                             const F& last = {}) {
     if constexpr (L > 1) {
       constexpr int R = FIRST ? Plan<N, RADIX>::FIRST : RADIX;
-      dif_stage<T, N, NL, NTHR, R, L, MAP>(buf, rt, tid);
-      DifRunner<T, N, NL, NTHR, L / R, false, RADIX, MAP>::run(buf, rt, tid);
+      dif_stage<T, N, NL, NTHR, R, L, MAP>(buf, rt, tid, last);
+      DifRunner<T, N, NL, NTHR, L / R, false, RADIX, MAP>::run(buf, rt, tid, last);
     }
   }
 };
@@ -249,9 +257,10 @@ struct DifRunner {
 // element e of line l lives at MAP::at(l N + e); input in natural order, bin k
 // found at element digit_rev<N, RADIX>(k). The caller must have synchronised
 // after writing the input; the FFT ends with a barrier.
-template <typename T, int N, int NL, int NTHR, int RADIX, typename MAP>
-__device__ __forceinline__ void fft_lines(LdsLine<T> buf, const Roots<T, N>& rt, int tid) {
-  DifRunner<T, N, NL, NTHR, N, true, RADIX, MAP>::run(buf, rt, tid);
+template <typename T, int N, int NL, int NTHR, int RADIX, typename MAP, typename F = NoHook>
+__device__ __forceinline__ void fft_lines(LdsLine<T> buf, const Roots<T, N>& rt, int tid,
+                                          const F& last = {}) {
+  DifRunner<T, N, NL, NTHR, N, true, RADIX, MAP>::run(buf, rt, tid, last);
 }
 
 // Element holding DFT bin k after fft_lines: the mixed-radix digits of k

@@ -11,7 +11,8 @@
 //       rows (the band's rows of a column pair leave as one piece per FP64
 //       field or FP32 field pair).
 //   P2  k_col_gram   : per column, DCT-II along y of its fields (two as one
-//       complex line) and the Parseval inner products (F_i, chi^{-1} F_j), (P, zeta^{-1} g), (P, zeta^{-1} L).
+//       complex line, brought to one size) and the Parseval inner products
+//       (F_i, chi^{-1} F_j), (P, zeta^{-1} g), (P, zeta^{-1} L).
 //   S   k_solve      : reduces the partials, assembles and solves the 5x5
 //       system of App. B Step 4, updates the SAVs, and emits the spectral
 //       combination coefficients (all on the device).
@@ -83,14 +84,17 @@ template <typename TM> constexpr int line_threads_v(int n, int v) {
 // thread, so that four kept FP32 spectra take 32 registers and two workgroups
 // of 512 threads fit a CU at N = 4096. FP32 lines of 8192 points take sixteen
 // bins and radix-16 butterflies: one workgroup per CU either way (1024
-// threads: 1594 us, 512: 1499; 1268 with 16-byte LDS accesses).
+// threads: 1594 us, 512: 1499; 1301 now).
 template <typename TM> constexpr int gram_threads(int n) {
   return clamp_threads(n / (sizeof(TM) == 4 && n >= 8192 ? 16 : 8));
 }
 // Waves per SIMD the Gram kernel's registers are held to: it is bound by issue
 // and by barriers, so lines of 2048 and 4096 points take four at 128 registers
 // (with 8-byte LDS accesses N = 4096 FP64: 475 us against 590 at two, N = 2048
-// FP32 66 against 78; 421 and 58 now).
+// FP32 66 against 78; 442 and 61 now). Lines of 8192 points have one workgroup
+// to a CU by their LDS (FP32: two waves per SIMD) or four waves by its 1024
+// threads (FP64); at 1024 points three or four waves spill (FP32 20 us in
+// place of 24 and 44), and shorter lines have the registers to spare.
 constexpr int gram_waves(int n) { return n == 2048 || n == 4096 ? 4 : 1; }
 // Complex lines of length n that fit in LDS next to the twiddle tables.
 template <typename TM> constexpr int lds_line_budget(int n) {
@@ -156,6 +160,25 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Maximum of values >= 0 over each row of 16 lanes (in its lane 15) and over
+// the wave (the same in every lane), all lanes active, by DPP row shifts and
+// broadcasts.
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_max(int v) {
+  return max(v, __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ int row_max(int v) {
+  v = dpp_max<0x111, 0xf>(v);       // row_shr 1, 2, 4, 8
+  v = dpp_max<0x112, 0xf>(v);
+  v = dpp_max<0x114, 0xf>(v);
+  return dpp_max<0x118, 0xf>(v);
+}
+__device__ __forceinline__ int wave_max(int v) {
+  v = row_max(v);
+  v = dpp_max<0x142, 0xa>(v);       // row_bcast 15 into rows 1 and 3
+  v = dpp_max<0x143, 0xc>(v);       // row_bcast 31 into rows 2 and 3
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 // Sum NV doubles over the block in a fixed order; the totals land in red[0..NV).
@@ -951,11 +974,12 @@ __device__ __forceinline__ void fetch_strip_first(gptr<const cpx<TM>> __restrict
 // TRAIL_SYNC false: the caller writes its next line elsewhere, so the last
 // reads of this one need no barrier behind them.
 template <typename TM, int NY, int LPT, int UPT, int NTHR, int R, typename MAP,
-          bool FIRST_IN_REGS = false, bool TRAIL_SYNC = true>
+          bool FIRST_IN_REGS = false, bool TRAIL_SYNC = true, typename F = NoHook>
 __device__ __forceinline__ void column_dct2(const StripRegs<TM, LPT>& in, LdsLine<TM> line,
                                             const Roots<TM, NY>& rt,
                                             const LineSlots<NY, NTHR, R, MAP>& sl, int tid,
-                                            TM (&A)[2 * UPT], TM (&B)[2 * UPT]) {
+                                            TM (&A)[2 * UPT], TM (&B)[2 * UPT],
+                                            const F& last = {}) {
   if constexpr (FIRST_IN_REGS) {
     static_assert(LPT == R && first_stage_in_registers<NY, NTHR, R>(), "one butterfly per thread");
     // the first stage of fft_lines (block length NY, stride NY/R) on butterfly tid
@@ -969,14 +993,14 @@ __device__ __forceinline__ void column_dct2(const StripRegs<TM, LPT>& in, LdsLin
 #pragma unroll
     for (int q = 0; q < R; ++q) line[e ^ MAP::at(q * S)] = v[q];
     lds_sync();
-    DifRunner<TM, NY, 1, NTHR, S, false, R, MAP>::run(line, rt, tid);
+    DifRunner<TM, NY, 1, NTHR, S, false, R, MAP>::run(line, rt, tid, last);
   } else {
     static_for<LPT>([&](auto iq) {
       constexpr int q = decltype(iq)::value;
       if (NY >= NTHR || tid + q * NTHR < NY) line[sl.template mak<q>()] = in.v[q];
     });
     lds_sync();
-    fft_lines<TM, NY, 1, NTHR, R, MAP>(line, rt, tid);
+    fft_lines<TM, NY, 1, NTHR, R, MAP>(line, rt, tid, last);
   }
   static_for<UPT>([&](auto iq) {
     constexpr int q = decltype(iq)::value;
@@ -1027,7 +1051,19 @@ template <typename TM, int NY> struct GramLds {
   cpx<TM> line[GP::LINE > GP::SUMS ? GP::LINE : GP::SUMS];
   cpx<double> rtab[Roots<TM, NY>::SIZE];
   double wsum[GP::WAVES][P2_NSUM];
+  int top[4][2];                   // largest values of the four pairs (size_word)
 };
+
+// x >= 0 as an ordered integer with the exponent on top (FP64: the upper half).
+__device__ __forceinline__ int size_word(float x) { return __float_as_int(x); }
+__device__ __forceinline__ int size_word(double x) { return __double2hiint(x); }
+template <typename TM> __device__ __forceinline__ TM pow2(int e);
+template <> __device__ __forceinline__ float pow2<float>(int e) {
+  return __int_as_float((127 + e) << 23);
+}
+template <> __device__ __forceinline__ double pow2<double>(int e) {
+  return __hiloint2double((1023 + e) << 20, 0);
+}
 
 // The Gram pass of column k. The eight fields go through the transform in
 // four pairs, two fields of the column as one complex line. A column at a
@@ -1037,7 +1073,8 @@ template <typename TM, int NY> struct GramLds {
 // columns of a strip read its rows; the second read is served by the L2 (the
 // counted HBM traffic is that of one). At N = 4096 (FP32, 248 us; two columns
 // per workgroup 253 us, two side by side in one of 1024 threads 290, radix 16
-// with 256 threads 272; 233 us since the roots move with 16-byte LDS accesses)
+// with 256 threads 272; 250 us now that the roots move with 16-byte LDS accesses
+// and the pairs are balanced)
 // the VALU issues 77% of the time and the LDS is busy for 36%.
 // FRESH_SLOTS: every transform forms its LDS slots anew (the persistent
 // launch, where the kernel's register budget is shared by all passes).
@@ -1058,6 +1095,7 @@ __device__ __forceinline__ void col_gram_body(gptr<const TM> __restrict__ mid,
   using LS = LineSlots<NY, NTHR, GR, MAP>;
   Roots<TM, NY> rt;
   rt.init(L.rtab, tid, NTHR);
+  if (tid < 8) L.top[tid >> 1][tid & 1] = 0;
   // a first stage from registers looks the roots up before any other barrier
   lds_sync();
   const LS sl(tid);
@@ -1102,6 +1140,42 @@ __device__ __forceinline__ void col_gram_body(gptr<const TM> __restrict__ mid,
   constexpr bool AHEAD = GP::AHEAD && !FRESH_SLOTS;
   StripRegs<TM, LPT> next;
   if constexpr (AHEAD) fetch(std::integral_constant<int, 0>{}, tid, next);
+  // The rounding errors of a complex transform are relative to the larger of
+  // the two fields in it, and the fields of a column differ by factors up to
+  // thousands (Q~ and K~, f_lin and P~). The second one is therefore brought to
+  // the first one's size by a power of two (exact, and undone exactly), from
+  // the largest values over the column: unscaled, the inner products of Q~ were
+  // off by up to 25 times as much (FP32, 64^2). A field of zeros gets a spectrum
+  // of zeros. It costs about 60 vector instructions a pair and a barrier where
+  // nothing is loaded ahead: N = 4096 mixed 233 -> 250 us and FP64 417 -> 442,
+  // N = 8192 mixed 1266 -> 1301, N = 2048 mixed 58 -> 61 (the waves' parts by
+  // shared memory alone, without the lane shifts: 285 at N = 4096).
+  const int lane = tid & 63, wave = tid >> 6;
+  // the pair's largest values; of several waves in L.top, behind a barrier
+  auto sizes = [&](const StripRegs<TM, LPT>& r, int p, int& ta, int& tb) {
+    TM ma = (TM)0, mb = (TM)0;
+#pragma unroll
+    for (int q = 0; q < LPT; ++q) {
+      ma = fmax(ma, fabs(r.v[q].re));
+      mb = fmax(mb, fabs(r.v[q].im));
+    }
+    ta = size_word(ma);
+    tb = size_word(mb);
+    if constexpr (GP::WAVES == 1) {
+      ta = wave_max(ta);
+      tb = wave_max(tb);
+    } else {
+      ta = row_max(ta);
+      tb = row_max(tb);
+      // (an address that looks different in each lane: the compiler makes a
+      // loop over the lanes of an atomic to a common one)
+      int* top = &L.top[opaque_vgpr(p)][0];
+      if ((lane & 15) == 15) {
+        __hip_atomic_fetch_max(top, ta, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_max(top + 1, tb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+  };
   auto transform = [&](auto ip, TM (&A)[KPT], TM (&B)[KPT]) {
     constexpr int p = decltype(ip)::value;
     constexpr bool FRESH = GP::FRESH || FRESH_SLOTS;
@@ -1113,14 +1187,42 @@ __device__ __forceinline__ void col_gram_body(gptr<const TM> __restrict__ mid,
     } else {
       fetch(ip, t, cur);
     }
+    int ta, tb;
+    if constexpr (!AHEAD || p == 0) {
+      sizes(cur, p, ta, tb);
+      if constexpr (GP::WAVES > 1) lds_sync();
+    }
+    if constexpr (GP::WAVES > 1) {
+      ta = __builtin_amdgcn_readfirstlane(L.top[p][0]);
+      tb = __builtin_amdgcn_readfirstlane(L.top[p][1]);
+    }
+    constexpr int MANT = sizeof(TM) == 4 ? 23 : 20, MOST = sizeof(TM) == 4 ? 120 : 1000;
+    int e = (ta >> MANT) - (tb >> MANT);
+    if ((unsigned)(e + MOST) > 2u * MOST) e = e < 0 ? -MOST : MOST;
+    if (ta == 0 || tb == 0) e = 0;
+    const TM up = pow2<TM>(e), down = tb == 0 ? (TM)0 : pow2<TM>(-e);
+#pragma unroll
+    for (int q = 0; q < LPT; ++q) cur.v[q].im *= up;
+    // loads ahead: the next pair's sizes ahead of a barrier that is there
+    auto last = [&]() {
+      int na, nb;
+      if constexpr (AHEAD && p < 3) sizes(next, p + 1, na, nb);
+    };
     cpx<TM>* ln = GP::DBL ? L.line + (p % 2) * NY : L.line;
     if constexpr (FRESH) {
       const LS slt(t);
       column_dct2<TM, NY, LPT, UPT, NTHR, GR, MAP, FIRST_IN_REGS, !GP::DBL>(cur, ln, rt, slt, t,
-                                                                          A, B);
+                                                                          A, B, last);
     } else {
       column_dct2<TM, NY, LPT, UPT, NTHR, GR, MAP, FIRST_IN_REGS, !GP::DBL>(cur, ln, rt, sl, t,
-                                                                          A, B);
+                                                                          A, B, last);
+    }
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) B[j] *= down;
+    if (__builtin_expect(ta == 0, 0)) {
+      __asm__ volatile("");            // a branch, not a selection for every value
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) A[j] *= (TM)0;       // (a NaN, not seen by fmax, stays)
     }
   };
   double v[P2_NSUM];
@@ -1190,7 +1292,6 @@ __device__ __forceinline__ void col_gram_body(gptr<const TM> __restrict__ mid,
   // The block's sums, through the line buffer (no longer read): each wave
   // takes four sums at a time, 16 lanes adding four lanes' values each and
   // then pairwise; the waves' totals are added in order.
-  const int lane = tid & 63, wave = tid >> 6;
   double* buf = reinterpret_cast<double*>(L.line) + wave * 256;
   lds_sync();
 #pragma unroll
