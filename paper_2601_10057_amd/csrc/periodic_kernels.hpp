@@ -104,11 +104,14 @@ k_per_cols(PerCols f, int nx, size_t cs, PerConst c) {
     cpx<double>* out = op == 0 ? f.chi[blockIdx.y] : f.zeta[blockIdx.y];
     if (!out) continue;                          // uniform over the workgroup
     for (int k = tid; k < NY; k += NTHR) {
-      const double sy = rt.omega64(2 * k).im;    // -sin(pi k / ny)
+      // (From the root table the sine would be off by up to 5e-15 near k = ny,
+      // and k and ny - k would differ: 78 us a step at N = 512, 80 so. The
+      // eigenvalues of all modes at once, ahead of the transform: 82.)
+      const double sy = sinpi((double)k / NY);
       const double L = lx + h4 * sy * sy;
-      const double s = rcp64(op == 0 ? c.C1 + L * (c.C2 + c.C3 * L) : c.alpha + c.lam * L);
+      const double s = op == 0 ? c.C1 + L * (c.C2 + c.C3 * L) : c.alpha + c.lam * L;
       const cpx<double> x = a[per_slot<NY>(k)];
-      b[MAP::at(k)] = {x.re * s, -x.im * s};     // conjugate of X / s
+      b[MAP::at(k)] = {x.re / s, -x.im / s};     // conjugate of X / s
     }
     lds_sync();
     fft_lines<double, NY, 1, NTHR, 8, MAP>(b, rt, tid);
