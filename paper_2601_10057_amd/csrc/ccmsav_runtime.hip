@@ -1544,6 +1544,19 @@ bool on_device(const void* p, int dev) {
   return (at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged) && at.device == dev;
 }
 
+// Whether `bytes` from p on lie in one allocation of device dev.
+bool holds_on_device(const void* p, size_t bytes, int dev) {
+  if (!on_device(p, dev)) return false;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const size_t off = static_cast<const char*>(p) - static_cast<const char*>(base);
+  return off <= size && bytes <= size - off;
+}
+
 }  // namespace
 
 // Scratch memory of ccmsav_elliptic_solve_noalloc: a fixed array on every
@@ -1938,10 +1951,12 @@ int ccmsav_get_fields_m(ccmsav_ctx* c, int32_t member, double* phi, double* psi)
   const size_t cells = (size_t)m.p.nx * m.p.ny, bytes = cells * sizeof(double);
   const int s = (int)(c->level % 3);
   // outputs in the context's device's memory leave in one kernel with the
-  // error bits
+  // error bits (one that does not hold a field is left to the copies, which
+  // refuse it)
   int dev = -1;
   HIP_TRY(hipGetDevice(&dev));
-  if (c->host_err && dev == c->device && (!phi || on_device(phi, dev)) && (!psi || on_device(psi, dev))) {
+  if (c->host_err && dev == c->device && (!phi || holds_on_device(phi, bytes, dev)) &&
+      (!psi || holds_on_device(psi, bytes, dev))) {
     const int blocks = (int)std::min<size_t>((cells / 2 + EXPORT_THREADS - 1) / EXPORT_THREADS, 4096);
     hipLaunchKernelGGL(k_export, dim3(blocks), dim3(EXPORT_THREADS), 0, c->stream, m.phi[s],
                        m.psi[s], phi, psi, cells, &m.ds->err,

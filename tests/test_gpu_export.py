@@ -70,3 +70,31 @@ def test_contexts_beyond_the_pinned_words_query_as_well():
         ctx.fields_into(phi, psi)
         assert all(np.array_equal(a.cpu().numpy(), b) for a, b in zip((phi, psi), ref))
         ctx.close()
+
+
+def test_a_device_output_that_does_not_hold_the_field_is_refused():
+    # 12 MB for fields of 32 MB, an allocation of its own
+    m = vesicle_member(64, 3)
+    p = dict(m.params, nx=2048, ny=2048)
+    phi = torch.full((2048, 2048), 0.3, device="cuda", dtype=torch.float64)
+    with C.Context(p, phi, phi + 0.8) as ctx:
+        ctx.step(1)
+        torch.cuda.empty_cache()
+        small = torch.full((3 << 19,), -7.0, device="cuda", dtype=torch.float64)
+        at = small.data_ptr()
+        seg = [s for s in torch.cuda.memory_snapshot()
+               if s["address"] <= at < s["address"] + s["total_size"]]
+        if not seg or seg[0]["address"] + seg[0]["total_size"] - at >= 8 * phi.numel():
+            pytest.skip("the allocator placed the output in a larger allocation")
+        for outs in ((small, None), (None, small), (phi, small)):
+            with pytest.raises(C.CcmsavError) as e:
+                ctx.fields_into(*outs)
+            assert e.value.name == "EHIP"
+            try:                            # the runtime reports the refusal once more
+                torch.ones(1, device="cuda")
+            except RuntimeError:
+                pass
+            assert (small == -7.0).all()
+        got = torch.empty_like(phi)
+        ctx.fields_into(got, None)
+        assert np.array_equal(got.cpu().numpy(), ctx.fields()[0])
