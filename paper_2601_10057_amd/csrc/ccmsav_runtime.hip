@@ -1952,10 +1952,12 @@ int ccmsav_get_fields_m(ccmsav_ctx* c, int32_t member, double* phi, double* psi)
   const int s = (int)(c->level % 3);
   // outputs in the context's device's memory leave in one kernel with the
   // error bits (one that does not hold a field is left to the copies, which
-  // refuse it)
+  // refuse it, and so are outputs that overlap, where psi comes last)
   int dev = -1;
   HIP_TRY(hipGetDevice(&dev));
-  if (c->host_err && dev == c->device && (!phi || holds_on_device(phi, bytes, dev)) &&
+  const uintptr_t at = reinterpret_cast<uintptr_t>(phi), to = reinterpret_cast<uintptr_t>(psi);
+  const bool apart = !phi || !psi || (at < to ? to - at : at - to) >= bytes;
+  if (c->host_err && dev == c->device && apart && (!phi || holds_on_device(phi, bytes, dev)) &&
       (!psi || holds_on_device(psi, bytes, dev))) {
     const int blocks = (int)std::min<size_t>((cells / 2 + EXPORT_THREADS - 1) / EXPORT_THREADS, 4096);
     hipLaunchKernelGGL(k_export, dim3(blocks), dim3(EXPORT_THREADS), 0, c->stream, m.phi[s],

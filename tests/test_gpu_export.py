@@ -98,3 +98,19 @@ def test_a_device_output_that_does_not_hold_the_field_is_refused():
         got = torch.empty_like(phi)
         ctx.fields_into(got, None)
         assert np.array_equal(got.cpu().numpy(), ctx.fields()[0])
+
+
+@pytest.mark.parametrize("shift", [0, 1, 777, 2048, 4095, -1, -2048])
+def test_outputs_that_overlap_hold_psi(shift):
+    # psi starts `shift` values behind phi and is written last
+    m = vesicle_member(64, 8, dt=2.5e-8)
+    with C.Context(m.params, m.phi0, m.psi0) as ctx:
+        ctx.step(2)
+        want_phi, want_psi = (torch.from_numpy(f.ravel()) for f in ctx.fields())
+        for _ in range(20):
+            buf = torch.zeros(3 * 4096, device="cuda", dtype=torch.float64)
+            ctx.fields_into(buf[4096:8192], buf[4096 + shift:8192 + shift])
+            want = torch.zeros(3 * 4096, dtype=torch.float64)
+            want[4096:8192] = want_phi
+            want[4096 + shift:8192 + shift] = want_psi
+            assert torch.equal(buf.cpu(), want)
