@@ -1960,10 +1960,15 @@ int ccmsav_get_fields_m(ccmsav_ctx* c, int32_t member, double* phi, double* psi)
   if (c->host_err && dev == c->device && apart && (!phi || holds_on_device(phi, bytes, dev)) &&
       (!psi || holds_on_device(psi, bytes, dev))) {
     const int blocks = (int)std::min<size_t>((cells / 2 + EXPORT_THREADS - 1) / EXPORT_THREADS, 4096);
-    hipLaunchKernelGGL(k_export, dim3(blocks), dim3(EXPORT_THREADS), 0, c->stream, m.phi[s],
-                       m.psi[s], phi, psi, cells, &m.ds->err,
-                       c->persistent && c->bar ? &c->bar->err : nullptr, c->host_err);
-    if (hipGetLastError() != hipSuccess) return CCMSAV_EHIP;
+    // (by the launch's own status: an error that an earlier call of the
+    // program left is not this one's)
+    const double *src_phi = m.phi[s], *src_psi = m.psi[s];
+    const int* err = &m.ds->err;
+    const unsigned* bar_err = c->persistent && c->bar ? &c->bar->err : nullptr;
+    size_t n = cells;
+    void* args[] = {&src_phi, &src_psi, &phi, &psi, &n, &err, &bar_err, &c->host_err};
+    HIP_TRY(hipLaunchKernel(reinterpret_cast<const void*>(&k_export), dim3(blocks),
+                            dim3(EXPORT_THREADS), args, 0, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return status_from_err(c->host_err[0] | (c->host_err[1] ? ERR_BARRIER : 0));
   }

@@ -1,6 +1,8 @@
 """Field queries to device memory (one kernel with the error bits) give the bytes that queries to
 host memory give: both fields, either one alone, members of several grids, and destinations at an
 8-byte offset; a state that is not finite is reported either way."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -114,3 +116,20 @@ def test_outputs_that_overlap_hold_psi(shift):
             want[4096:8192] = want_phi
             want[4096 + shift:8192 + shift] = want_psi
             assert torch.equal(buf.cpu(), want)
+
+
+def test_an_error_that_another_call_left_does_not_fail_the_query():
+    m = vesicle_member(64, 11, dt=2.5e-8)
+    with C.Context(m.params, m.phi0, m.psi0) as ctx:
+        ctx.step(2)
+        want = ctx.fields()
+        phi, psi = (torch.zeros(64, 64, device="cuda", dtype=torch.float64) for _ in range(2))
+        host = np.zeros((64, 64))
+        torch.cuda.synchronize()
+        # a device number that does not exist sets the error state
+        hip = [line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line]
+        assert ctypes.CDLL(hip[0]).hipSetDevice(9999) != 0
+        ctx.fields_into(phi, psi)
+        assert all(np.array_equal(a.cpu().numpy(), b) for a, b in zip((phi, psi), want))
+        ctx.fields_into(host, None)
+        assert np.array_equal(host, want[0])
