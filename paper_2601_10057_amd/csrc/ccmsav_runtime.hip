@@ -457,6 +457,7 @@ struct SizeClass {
   int count;
   const int* d_idx;
   StencilShape sh;
+  int part_rows;                 // rows of partial sums, the longer of the two arrays
   int var[kNumTuned];            // chosen launch variant of each tuned kernel
   float tune_ms[kNumTuned][kNumVariants];   // best measured time of each variant
 };
@@ -728,16 +729,12 @@ void enqueue_classical_solves(ccmsav_ctx* c, int table, hipStream_t st) {
 
 // The 5x5 kernel of `count` members of class k, with the thread count and
 // the slicing of their grid size (every path of a grid uses the same, so
-// results agree). Grids of 1024^2 cells and more reduce their thousands of
-// partial rows over SOLVE_SLICES workgroups each: at N = 1024 11.5 us against
-// 14.5 us for one workgroup (at N = 512 one workgroup takes 10.4), at N =
-// 4096 13.6 us.
+// results agree).
 void launch_solve(hipStream_t st, const SizeClass& k, int count, const MemberArgs* tab) {
-  const size_t cells = (size_t)1 << (k.lx + k.ly);
-  if (cells >= (size_t)1024 * 1024)
+  if (solve_sliced(k.part_rows))
     hipLaunchKernelGGL(k_solve_sliced<SOLVE_THREADS>, dim3(count * SOLVE_SLICES),
                        dim3(SOLVE_THREADS), 0, st, tab, k.d_idx, SOLVE_SLICES);
-  else if (solve_threads(cells) == SOLVE_THREADS)
+  else if (solve_threads(1 << k.lx, 1 << k.ly) == SOLVE_THREADS)
     hipLaunchKernelGGL(k_solve<SOLVE_THREADS>, dim3(count), dim3(SOLVE_THREADS), 0, st, tab,
                        k.d_idx, 1);
   else
@@ -1019,7 +1016,8 @@ int build_persist_plan(ccmsav_ctx* c) {
   for (size_t ki = 0; ki < c->cls.size(); ++ki) {
     const SizeClass& k = c->cls[ki];
     // every member of the class takes the 256-thread 5x5 kernel in both paths
-    if (solve_threads((size_t)1 << (k.lx + k.ly)) != SOLVE_THREADS_SMALL) return CCMSAV_EUNSUPPORTED;
+    if (solve_sliced(k.part_rows) || solve_threads(1 << k.lx, 1 << k.ly) != SOLVE_THREADS_SMALL)
+      return CCMSAV_EUNSUPPORTED;
     // one wave per unit: the workgroups of the unsplit stencil pass
     const int sblocks = (k.sh.units + SW_WAVES - 1) / SW_WAVES;
     pl.cls[ki] = PersistClass{k.lx, k.ly, k.count, k.d_idx, sblocks};
@@ -1762,7 +1760,8 @@ int ccmsav_init_batch(ccmsav_ctx** out, int32_t nmemb, const ccmsav_params* p,
     bool seen = false;
     for (const SizeClass& k : c->cls) seen = seen || (k.lx == c->mem[mi].lx && k.ly == c->mem[mi].ly);
     if (seen) continue;
-    SizeClass k{c->mem[mi].lx, c->mem[mi].ly, 0, nullptr, c->mem[mi].sh, {0, 0, 1}, {}};
+    SizeClass k{c->mem[mi].lx, c->mem[mi].ly, 0, nullptr, c->mem[mi].sh,
+                (int)std::max<size_t>(c->mem[mi].sh.units, p2_rows(&c->mem[mi].p)), {0, 0, 1}, {}};
     const int start = (int)order.size();
     for (int32_t mj = mi; mj < nmemb; ++mj)
       if (c->mem[mj].lx == k.lx && c->mem[mj].ly == k.ly) order.push_back(mj);

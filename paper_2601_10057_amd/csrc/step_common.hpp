@@ -67,8 +67,8 @@ enum ErrBits {
 
 // Device-resident scalar state. Everything the time loop needs lives here so
 // that a step never waits on the host.
-// Workgroups of the 5x5 kernel per grid of 1024^2 cells or more, each
-// reducing a slice of the partial rows.
+// Workgroups of the 5x5 kernel per grid of many partial rows (solve_sliced),
+// each reducing a slice of them.
 constexpr int SOLVE_SLICES = 16;
 
 struct DevScalars {
@@ -81,7 +81,7 @@ struct DevScalars {
   double cl[2];          // classical scheme: (P~, zeta^{-1} g), (P~, zeta^{-1} L~)
   int err;
   int pad[3];
-  // 5x5 kernel over several workgroups (grids of 1024^2 cells or more): the
+  // 5x5 kernel over several workgroups (solve_sliced): the
   // column sums of each slice of the partial rows, and the slices done in the
   // current step
   double slice[SOLVE_SLICES][P1_NSUM + P2_NSUM];

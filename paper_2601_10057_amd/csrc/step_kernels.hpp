@@ -1373,14 +1373,20 @@ __device__ void reduce_columns(P part, int nrows, double* red, int tid, double (
 // ---------------------------------------------------------------------------
 // S: the 5x5 reduced system of App. B, Step 4, and the SAV update.
 // ---------------------------------------------------------------------------
-// Threads of the 5x5 kernel: 512 for grids above 512^2 (thousands of partial
-// rows, read with many loads in flight), 256 up to 512^2. The two orders of
-// the partial sums differ, so every path of one grid uses the same count.
+// Threads of the 5x5 kernel: 512, and 256 on grids of at most 512 per
+// direction, as in the persistent launch. The two orders of the partial sums
+// differ, so every path of one grid uses the same count. Grids with more than
+// 1024 rows of partials in either array reduce them over SOLVE_SLICES
+// workgroups: it is the rows that count, not the cells. In us, one workgroup of
+// 256 threads, of 512 and the slices: 10.3, 9.4 and 10.9 at 512^2 (512 rows),
+// 12.2, 10.1 and 10.4 at 1024 x 128 (1024), 14.2, 12.2 and 11.0 at 512 x 1024
+// (1152), 17.2, 14.2 and 11.4 at 1024^2 (1548), 29.4, 19.7 and 11.4 at 4096 x 64.
 constexpr int SOLVE_THREADS = 512;
 constexpr int SOLVE_THREADS_SMALL = 256;
-inline int solve_threads(size_t cells) {
-  return cells > (size_t)512 * 512 ? SOLVE_THREADS : SOLVE_THREADS_SMALL;
+inline int solve_threads(int nx, int ny) {
+  return nx > 512 || ny > 512 ? SOLVE_THREADS : SOLVE_THREADS_SMALL;
 }
+inline bool solve_sliced(int rows) { return rows > 1024; }
 static_assert((int)P1_NSUM == 16 && (int)P2_NSUM == 16, "rows of 16 sums in both passes");
 template <int NTHR> struct SolveLds {
   double red[NTHR + 32];
