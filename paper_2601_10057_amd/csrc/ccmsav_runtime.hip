@@ -99,7 +99,7 @@ template <typename TM> struct Launch {
   }
   using S = void (*)(hipStream_t, const SolveArgs&);
   template <int N> static void solve_rows(hipStream_t st, const SolveArgs& a) {
-    hipLaunchKernelGGL((k_solve_rows<TM, N>), dim3(a.ny / 2), dim3(line_threads(N)), 0, st, a);
+    hipLaunchKernelGGL((k_solve_rows<TM, N>), dim3(a.ny / solve_line_rows<TM>()), dim3(line_threads(N)), 0, st, a);
   }
   template <int N> static void solve_cols(hipStream_t st, const SolveArgs& a) {
     hipLaunchKernelGGL((k_solve_cols<TM, N>), dim3(a.nx / 2, solve_split(a.nx, a.ny) ? 2 : 1),

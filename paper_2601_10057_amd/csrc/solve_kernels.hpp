@@ -1,7 +1,7 @@
 // The fast direct solver of App. C on its own: chi^{-1} and zeta^{-1} of one
 // real field, with the DCT (homogeneous Neumann boundaries) or the DST
 // (homogeneous Dirichlet ones).
-//   k_solve_rows  two rows as one complex line, DCT-II along x
+//   k_solve_rows  DCT-II along x, in FP64 of two rows as one complex line
 //   k_solve_cols  per strip of two columns: DCT-II along y once, then for
 //                 each operator the divide and the DCT-III along y
 //   k_solve_inv   DCT-III along x of both results (the step's row inverse)
@@ -37,11 +37,17 @@ struct SolveArgs {
   OpConst k;
 };
 
-// A field has two real rows to a complex line (one row per line, half of each
-// transform idle: 27 us at N = 2048 in FP64, 24 us so), and a column pair's
-// rows leave as one piece.
+// FP64: two real rows to a complex line (one row per line, half of each
+// transform idle: 27 us at N = 2048, 24 us so; a solve at N = 4096 495 us, 457
+// so), and a column pair's rows leave as one piece. The rounding errors of a
+// line are relative to its larger row, which costs a solve up to 5% more error
+// in the root mean square. FP32: one row to a line. With two, solves were off
+// by up to 1.5 times as much (16 x 4096, Dirichlet; 0.3 to 4% elsewhere); one
+// takes 80 us at N = 2048 in place of 73, and 357 at N = 4096 in place of 328.
+template <typename TM> constexpr int solve_line_rows() { return sizeof(TM) == 8 ? 2 : 1; }
 template <typename TM, int NX>
 __global__ void __launch_bounds__(line_threads(NX)) k_solve_rows(SolveArgs a) {
+  constexpr int ROWS = solve_line_rows<TM>();
   constexpr int NTHR = line_threads(NX);
   constexpr int CPT = NX >= NTHR ? NX / NTHR : 1;
   constexpr int R = fft_radix<TM>();
@@ -50,7 +56,7 @@ __global__ void __launch_bounds__(line_threads(NX)) k_solve_rows(SolveArgs a) {
   __shared__ LinesLds<TM, NX, NX> L;
   const LdsLine<TM> line(L.line);
   const int tid = threadIdx.x;
-  const int j = 2 * xcd_remap(blockIdx.x, gridDim.x);
+  const int j = ROWS * xcd_remap(blockIdx.x, gridDim.x);
   if (a.tables != TABLES_GIVEN) {
     for (int e = blockIdx.x * NTHR + tid; e < NX + a.ny; e += gridDim.x * NTHR) {
       const bool x = e < NX;
@@ -68,9 +74,8 @@ __global__ void __launch_bounds__(line_threads(NX)) k_solve_rows(SolveArgs a) {
     constexpr int q = decltype(iq)::value;
     const int i = tid + q * NTHR;
     if (NX >= NTHR || i < NX) {
-      // j is even: row j has the sign of column i, row j + 1 the other one
-      const double u = src[i], w = src[NX + i];
-      const bool neg0 = a.alt & i & 1, neg1 = a.alt & ~i & 1;
+      const double u = src[i], w = ROWS == 2 ? src[NX + i] : 0.0;
+      const bool neg0 = a.alt & (i + j) & 1, neg1 = a.alt & (i + j + 1) & 1;
       line[sl.template mak<q>()] = {(TM)(neg0 ? -u : u), (TM)(neg1 ? -w : w)};
     }
   });
@@ -79,12 +84,14 @@ __global__ void __launch_bounds__(line_threads(NX)) k_solve_rows(SolveArgs a) {
   const size_t SS = strip_stride(a.ny, sizeof(TM));
   const auto mid = static_cast<gptr<TM>>(a.mid);
   row_dct_pairs<TM, NX, NTHR, MAP>(line, rt, tid, [&](int sp, TM a0, TM a1, TM b0, TM b1) {
-    RowPiece<TM, 2> pc;
+    RowPiece<TM, ROWS> pc;
     pc.v[0] = a0;
     pc.v[1] = a1;
-    pc.v[2] = b0;
-    pc.v[3] = b1;
-    store_piece<TM, 2>(mid + (size_t)sp * SS + 2 * (size_t)j, pc);
+    if constexpr (ROWS == 2) {
+      pc.v[2] = b0;
+      pc.v[3] = b1;
+    }
+    store_piece<TM, ROWS>(mid + (size_t)sp * SS + 2 * (size_t)j, pc);
   });
 }
 
