@@ -179,6 +179,10 @@ size_t ccmsav_workspace_bytes_batch(int32_t nmemb, const ccmsav_params* p);
  * workspace: caller-owned device memory of ws_bytes >= ccmsav_workspace_bytes(p)
  *            that must outlive the context, or NULL to let the library allocate
  *            (and free at destroy).
+ * Beside it the library holds one allocation of 4 KB of pinned host memory per
+ * process, made with the first context and kept until the process ends: the
+ * words through which field queries to device memory report errors, for 256
+ * contexts at a time (the queries of further ones are plain copies, slower).
  * hip_stream: a hipStream_t (NULL = default stream).
  * Returns EINVAL (bad pointer or parameter), EUNSUPPORTED (size / precision),
  * ENOMEM, EHIP, or a device status of the initial reduction (ENONFINITE,
@@ -360,8 +364,8 @@ int ccmsav_elliptic_solve_bc(ccmsav_ctx* c, int32_t bc, const double* rhs, doubl
  *    streams, other host threads) race on that array: order them, for
  *    example on one stream.
  *  - Allocates nothing: no hipMalloc or hipFree and no host-to-device copy;
- *    the tables and the kernels' argument block are written by a kernel. The
- *    first call on a device looks up the array's device address.
+ *    the eigenvalue tables are formed by the first kernel. The first call on a
+ *    device looks up the array's device address.
  * Returns EINVAL (NULL rhs, bad parameter, a pointer that is not device memory
  * of the current device), EUNSUPPORTED (a grid beyond 1024 per direction,
  * the DCT-as-GEMM precision), EHIP.

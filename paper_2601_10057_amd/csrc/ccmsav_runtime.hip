@@ -533,16 +533,14 @@ MemberArgs member_args(const Member& m, int precision, int table) {
     // The classical scheme's preconditioner alpha - lambda M_bar Delta_h for
     // the residuals of both systems: slot M_F through the chi group and slot
     // M_G through the zeta group, the constants written on the device each
-    // step (k_cl_setup), outputs z of system 0 and 1; the kernels return at
-    // once after both systems have converged.
+    // step (k_cl_setup); the column solve returns at once after both systems
+    // have converged.
     a.k = make_const(m.p, true);
     a.coef = to_global<const double>(m.unit_coef);
     a.chi_base = M_F;
     a.nchi = 1;
     a.zeta_base = M_G;
     a.nzeta = 1;
-    a.phi_new = to_global(m.cl_z);
-    a.psi_new = to_global(m.cl_z ? m.cl_z + (size_t)m.p.nx * m.p.ny : nullptr);
     a.skip = to_global<const int>(m.cl_sc ? &m.cl_sc->done_all : nullptr);
     return a;
   }
@@ -1077,10 +1075,14 @@ int enqueue_step_level(ccmsav_ctx* c, int64_t level, hipStream_t st,
           if (mn < c->cls[ki].tune_ms[tk][best]) best = v;
         }
         // On its own, on rows long since in memory, the FP32 row DCT of long
-        // lines takes about the same time in both bands; behind the stencil the half one
-        // is faster (N = 4096: 293 and 295 us alone, 285 and 274 in a step;
-        // N = 2048: 78 and 78, 77 and 65), so near ties go to it (N = 8192:
-        // 1410 and 1580 us alone, 1390 and 1560).
+        // lines takes about the same time in both bands on large grids; behind
+        // the stencil the half one is faster (N = 4096: 293 and 295 us alone,
+        // 285 and 274 in a step; N = 2048: 78 and 78, 77 and 65), so near ties
+        // go to it. Elsewhere there are none: rectangles of few rows take the
+        // half band by far, alone and in a step (2048 x 16 24 and 14 us, 4096 x
+        // 256 47 and 30, 8192 x 256 61 and 50), 8192 x 1024 and 8192^2 the full
+        // one (159 and 182 us alone, 160 and 181 in a step; 1410 and 1570, 1390
+        // and 1600), and 4096 x 1024 is a tie in a step too (71 and 70).
         const float* ms = c->cls[ki].tune_ms[tk];
         if (tk == TUNE_ROW_DCT && c->precision == CCMSAV_MIXED && c->cls[ki].lx >= 11 &&
             ms[1] < 1.05f * ms[0])
@@ -1173,9 +1175,10 @@ int read_err(ccmsav_ctx* c, int* err) {
 }
 
 // Pairs of pinned words for the contexts' field queries, 256 of them in one 4 KB
-// allocation of the process: an allocation and a release of its own took 20 us
-// each, a sixth of what the creation of a small context takes. Contexts beyond
-// them do without (their queries copy).
+// allocation of the process, kept until it ends: an allocation and a release of
+// its own took 20 us each, a sixth of what the creation of a small context
+// takes. A context gives its pair back when it is destroyed. Contexts beyond
+// the 256 do without: their queries copy (25 us for 256^2 in place of 14).
 constexpr int kPinnedPairs = 256, kPinnedInts = 4;
 std::mutex g_pinned_mu;
 int* g_pinned = nullptr;

@@ -5,7 +5,7 @@
 
 namespace ccm {
 
-// Partial sums written by the stencil pass, one row per workgroup.
+// Partial sums written by the stencil pass, one row per unit.
 enum P1Sum {
   P1_RS = 0,      // sum (phi*^2 - 1 - beta)^2 / (4 eps)          -> r_S^2 / h^2
   P1_RW,          // sum 6 phi*^2 |grad phi*|^2 + (phi*^3-phi*)^2/eps^2 -> r_W^2 / h^2
@@ -182,14 +182,14 @@ struct MemberArgs {
   gptr<const double> psn;        // psi^n, psi^{n-1}, psi^{n-2}
   gptr<const double> psm;
   gptr<const double> psmm;
-  gptr<double> phi_new;          // level n+1 (or the outputs of a standalone solve)
+  gptr<double> phi_new;          // level n+1
   gptr<double> psi_new;
   gptr<const double> phi_base;   // increment form: phi^n, psi^n added to the increments
   gptr<const double> psi_base;
   gptr<void> rm;                 // 8 stencil fields, row-major
   gptr<void> mid;                // 8 x-transformed fields, strip-major
   gptr<void> outc;               // 2 y-solved fields, strip-major
-  gptr<double> part1;            // stencil partial sums, one row per workgroup
+  gptr<double> part1;            // stencil partial sums, one row per unit
   gptr<double> part2;            // column partial sums, one row per column
   gptr<const double> lamx;       // (4/h^2) sin^2(pi k / (2 n)) per direction
   gptr<const double> lamy;
@@ -198,7 +198,7 @@ struct MemberArgs {
   gptr<const double> coef;       // spectral combination (ds->coef, or unit weights)
   gptr<double> mob_e;            // classical scheme: M_psi at the east and north face
   gptr<double> mob_n;            //   of each cell (0 on the walls), written by the stencil
-  gptr<const int> skip;          // solve kernels return at once while *skip != 0
+  gptr<const int> skip;          // the column solve returns at once while *skip != 0
   int nx, ny;
   int iters, p1_blocks;          // stencil units: rows of each, number (rows of partial sums)
   int p2_rows;                   // rows of column partial sums

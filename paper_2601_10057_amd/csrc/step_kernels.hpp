@@ -1661,11 +1661,11 @@ __device__ __forceinline__ void col_solve_body(gptr<const TM> __restrict__ mid,
 
   // Combine the x-transformed right-hand sides of this group: field by field,
   // all of a field's loads in flight together (the number of fields is a
-  // compile-time constant for the step's groups: 5 for chi, 2 for zeta, and
-  // 1 in the classical scheme's preconditioner). FP32 intermediates come in pairs: a pair whose
-  // halves are consecutive slots of the group is loaded once (16 bytes a
-  // row) and both halves are added in slot order, so that the sums are those
-  // of the field-by-field order.
+  // compile-time constant for the step's groups: 5 for chi, 2 for zeta, and 1
+  // in the classical scheme's preconditioner, FP64). FP32 intermediates come in
+  // pairs: a pair whose halves are consecutive slots of the group is loaded
+  // once (16 bytes a row) and both halves are added in slot order, so that the
+  // sums are those of the field-by-field order.
   auto combine_pairs = [&](auto inf) {
     constexpr int NF = decltype(inf)::value;
     typedef TM tm4 __attribute__((ext_vector_type(4)));
@@ -1745,7 +1745,7 @@ __device__ __forceinline__ void col_solve_body(gptr<const TM> __restrict__ mid,
     combine(std::integral_constant<int, 5>{});
   } else if (nf == 2) {
     combine(std::integral_constant<int, 2>{});
-  } else {
+  } else if constexpr (sizeof(TM) == 8) {
     combine(std::integral_constant<int, 1>{});
   }
   lds_sync();
@@ -2155,7 +2155,6 @@ __global__ void __launch_bounds__(row_idct_threads<TM>(NX, V),
 k_row_idct(BATCH_PARAMS) {
   int blk;
   const MemberArgs& m = batch_member(tab, idx, per, blk);
-  if (m.skip && *m.skip) return;     // a converged iteration (whole workgroup)
   if constexpr (V == 0) {
     __shared__ RowIdctBandLds<TM, NX> L;
     row_idct_band_body<TM, NX>(static_cast<gptr<const TM>>(m.outc), m.phi_new, m.psi_new, m.ny,
