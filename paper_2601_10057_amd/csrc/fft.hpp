@@ -21,7 +21,8 @@ namespace ccm {
 // FP64 lines) then move with one 16-byte LDS access. By two 8-byte ones, at a
 // stride of 16 bytes, half of the banks idled, and the LDS bound the transforms:
 // Gram pass N = 8192 mixed 1480 -> 1268 us, N = 4096 mixed 247 -> 233 and FP64
-// 478 -> 421, N = 1024 FP64 37 -> 29 and row DCT 49 -> 43.
+// 478 -> 421, N = 1024 FP64 37 -> 29 (1301, 250, 440 and 31 with its pairs
+// balanced), row DCT N = 1024 FP64 49 -> 43.
 template <typename T> struct alignas(2 * sizeof(T)) cpx { T re, im; };
 
 // Workgroup barrier for LDS traffic only: waits for this wave's LDS operations

@@ -91,7 +91,7 @@ template <typename TM> constexpr int gram_threads(int n) {
 // Waves per SIMD the Gram kernel's registers are held to: it is bound by issue
 // and by barriers, so lines of 2048 and 4096 points take four at 128 registers
 // (with 8-byte LDS accesses N = 4096 FP64: 475 us against 590 at two, N = 2048
-// FP32 66 against 78; 442 and 61 now). Lines of 8192 points have one workgroup
+// FP32 66 against 78; 440 and 61 now). Lines of 8192 points have one workgroup
 // to a CU by their LDS (FP32: two waves per SIMD) or four waves by its 1024
 // threads (FP64); at 1024 points three or four waves spill (FP32 20 us in
 // place of 24 and 44), and shorter lines have the registers to spare.
@@ -1074,8 +1074,7 @@ template <> __device__ __forceinline__ double pow2<double>(int e) {
 // counted HBM traffic is that of one). At N = 4096 (FP32, 248 us; two columns
 // per workgroup 253 us, two side by side in one of 1024 threads 290, radix 16
 // with 256 threads 272; 250 us now that the roots move with 16-byte LDS accesses
-// and the pairs are balanced)
-// the VALU issues 77% of the time and the LDS is busy for 36%.
+// and the pairs are balanced) the VALU issues 77% of the time and the LDS is busy for 35%.
 // FRESH_SLOTS: every transform forms its LDS slots anew (the persistent
 // launch, where the kernel's register budget is shared by all passes).
 template <typename TM, int NY, bool FRESH_SLOTS = false>
@@ -1147,7 +1146,7 @@ __device__ __forceinline__ void col_gram_body(gptr<const TM> __restrict__ mid,
   // the largest values over the column: unscaled, the inner products of Q~ were
   // off by up to 25 times as much (FP32, 64^2). A field of zeros gets a spectrum
   // of zeros. It costs about 60 vector instructions a pair and a barrier where
-  // nothing is loaded ahead: N = 4096 mixed 233 -> 250 us and FP64 417 -> 442,
+  // nothing is loaded ahead: N = 4096 mixed 233 -> 250 us and FP64 417 -> 440,
   // N = 8192 mixed 1266 -> 1301, N = 2048 mixed 58 -> 61 (the waves' parts by
   // shared memory alone, without the lane shifts: 285 at N = 4096).
   const int lane = tid & 63, wave = tid >> 6;
