@@ -1175,10 +1175,12 @@ int read_err(ccmsav_ctx* c, int* err) {
 }
 
 // Pairs of pinned words for the contexts' field queries, 256 of them in one 4 KB
-// allocation of the process, kept until it ends: an allocation and a release of
-// its own took 20 us each, a sixth of what the creation of a small context
-// takes. A context gives its pair back when it is destroyed. Contexts beyond
-// the 256 do without: their queries copy (25 us for 256^2 in place of 14).
+// allocation of the process: an allocation and a release of its own took 20 us
+// each, a sixth of what the creation of a small context takes. A context gives
+// its pair back when it is destroyed; the allocation stays until the process
+// ends, as hipHostFree waits for the device, which the destruction of a context
+// on the caller's workspace does not. Contexts beyond the 256 do without: their
+// queries copy (25 us for 256^2 in place of 14).
 constexpr int kPinnedPairs = 256, kPinnedInts = 4;
 std::mutex g_pinned_mu;
 int* g_pinned = nullptr;
